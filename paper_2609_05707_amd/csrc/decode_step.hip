@@ -281,13 +281,6 @@ __device__ __forceinline__ double lane_theta(const u32x4_t (&th)[TN], int ds, in
   return __hiloint2double(static_cast<int>(tp[2 * (u & 1) + 1]), static_cast<int>(tp[2 * (u & 1)]));
 }
 
-// Value of lane k of this lane's quad (DPP quad_perm broadcast).
-template <int K>
-__device__ __forceinline__ float quad_bcast(float v) {
-  constexpr int ctrl = K | (K << 2) | (K << 4) | (K << 6);
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, false));
-}
-
 // Query fragments (B operand) of one row block from its loaded pieces,
 // rotated at pos in the fused step.  Pair j < D/2 is (x_j, x_{j+D/2}):
 // fragments ds and ds + DS/2.  quad: the four lanes of each lane quad hold
