@@ -23,7 +23,7 @@ struct LoadContextParams {
   const int64_t* ctx_off; const int32_t* ctx_len; int32_t* err_flag;
   const int32_t* instr_start; const int32_t* instr_len; int S;   // two-level batch: position base (S = 0: none)
   int64_t pool; int B, Hkv, D, max_ctx_len;
-  double inv_freq[kMaxHalfDim];
+  alignas(16) double inv_freq[kMaxHalfDim];
 };
 
 struct LoadSegmentsParams {
@@ -33,7 +33,7 @@ struct LoadSegmentsParams {
   const int32_t* ctx_len; const int32_t* q_start; int32_t* seg_len; int32_t* err_flag;
   const int32_t* instr_start; const int32_t* instr_len; int S;   // two-level batch: position base (S = 0: none)
   int B, Nt, Hkv, D, seg_cap;
-  double inv_freq[kMaxHalfDim];
+  alignas(16) double inv_freq[kMaxHalfDim];
 };
 
 struct AppendParams {

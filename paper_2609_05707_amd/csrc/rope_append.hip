@@ -11,23 +11,6 @@
 
 namespace ippd {
 
-// Rotate 8 consecutive pairs (x[j], x[j + D/2]) for j = j0..j0+7.
-template <typename T>
-__device__ __forceinline__ void rotate8(const T* __restrict__ src, T* __restrict__ dst, int j0, int half,
-                                        const float2* cs) {
-  float a[8], bb[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) { a[u] = to_f32<T>(src[j0 + u]); bb[u] = to_f32<T>(src[j0 + half + u]); }
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const float2 c = cs[j0 + u];
-    float x, y;
-    rope_rotate(a[u], bb[u], c.x, c.y, x, y);
-    dst[j0 + u] = from_f32<T>(x);
-    dst[j0 + half + u] = from_f32<T>(y);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Decode-step append: one workgroup per question, one 16-byte vector per
 // thread and item.  Item e of question i is
@@ -158,121 +141,201 @@ __global__ __launch_bounds__(1024) void append_kernel(AppendParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Context loader: workgroup per (prompt b, 64-token tile, kv head g).
+// Cache loaders: one workgroup of four waves per octet of tokens (one 8-token
+// value block) of a context, instruction or segment, all kv heads.
+//   waves 0, 1  keys: lane (token, 8 rotation pairs) evaluates its 8 angles
+//               once and rotates the pairs of every second head with them, 16
+//               bytes (fp32: 32) per load and store;
+//   waves 2, 3  values: an item is (head, 8 dims) of the 8 tokens, transposed
+//               in registers into 8 pieces of 8 tokens, 128 contiguous bytes
+//               (fp32: 256).
+// What bounds it is the copy itself, 4 bytes moved per byte of key: every
+// byte is loaded and stored once in 16-byte pieces, and the angles (~35
+// instructions each, fp64) are shared by the heads.  At 38.4k tokens of 8
+// heads x 128 (315 MB moved), bf16: 133 us with an angle, a 2-byte load and a
+// 2-byte store per element, through LDS for the values; LOADNOW.
 // ---------------------------------------------------------------------------
-constexpr int kLoadTile = 64;
+template <typename T> struct Oct { typedef T type __attribute__((ext_vector_type(8))); };
 
 template <typename T>
-__global__ __launch_bounds__(256) void load_context_kernel(LoadContextParams p, int tiles_per_prompt) {
-  __shared__ T s_v[kLoadTile][128 + 1];
-  const int g = blockIdx.y;
-  const int b = blockIdx.x / tiles_per_prompt;
-  const int tile = blockIdx.x - b * tiles_per_prompt;
-  const int64_t off = p.ctx_off[b];
-  const int len = p.ctx_len[b];
-  if (off < 0 || (off & 7) || len < 0 || len > p.max_ctx_len || off + len > p.pool) {
-    if (threadIdx.x == 0 && tile == 0 && g == 0) raise_flag(p.err_flag, kFlagBadLayout);
-    return;
-  }
-  const int t0 = tile * kLoadTile;
-  if (t0 >= len) return;
-  const int nt = min(kLoadTile, len - t0);
-  const int D = p.D, half = D / 2;
-  const int64_t base_pos = instr_pos_base(p.instr_start, p.instr_len, p.S, b);
-  const T* __restrict__ kr = static_cast<const T*>(p.k_raw);
-  const T* __restrict__ vr = static_cast<const T*>(p.v_raw);
-  T* __restrict__ ck = static_cast<T*>(p.ctx_k);
-  T* __restrict__ cvt = static_cast<T*>(p.ctx_vt);
-  for (int e = threadIdx.x; e < nt * half; e += blockDim.x) {
-    const int tt = e / half, j = e - tt * half;
-    const int t = t0 + tt;
-    float c, sn;
-    rope_cos_sin(base_pos + t, p.inv_freq[j], c, sn);
-    const int64_t src = ((off + t) * p.Hkv + g) * D;
-    const int64_t dst = (static_cast<int64_t>(g) * p.pool + off + t) * D;
-    float x, y;
-    rope_rotate(to_f32<T>(kr[src + j]), to_f32<T>(kr[src + j + half]), c, sn, x, y);
-    ck[dst + j] = from_f32<T>(x);
-    ck[dst + j + half] = from_f32<T>(y);
-  }
-  // values: transpose a [tokens][D] tile into 8-token column blocks through LDS
-  for (int e = threadIdx.x; e < nt * D; e += blockDim.x) {
-    const int tt = e / D, d = e - tt * D;
-    s_v[tt][d] = vr[((off + t0 + tt) * p.Hkv + g) * D + d];
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < nt * D; e += blockDim.x) {
-    const int d = e / nt, tt = e - d * nt;
-    cvt[vt_index(g, p.pool, D, off + t0 + tt, d)] = s_v[tt][d];
+struct OctetArgs {
+  const T* k_raw; const T* v_raw;   // [rows][Hkv][D]
+  T* k; T* vt;                      // regions of `region` tokens per head: [heads][region][D] and its blocked transpose
+  int64_t src_row;                  // row of the octet's first token in k_raw / v_raw
+  int64_t head0;                    // first token of head 0's region
+  int64_t region;
+  int64_t tok;                      // the octet's first token in the region (a multiple of 8)
+  int64_t pos;                      // its position
+  int n;                            // tokens of the octet: 1 .. 8
+  int Hkv;
+};
+
+// The lane's 8 frequencies (waves 0, 1: pairs 8 * (lane % (D / 16)) ..).
+template <int D>
+__device__ __forceinline__ void octet_theta(double (&theta)[8], const double* inv_freq) {
+  const double2* src = reinterpret_cast<const double2*>(inv_freq + (threadIdx.x % (D / 16)) * 8);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const double2 x = src[u];
+    theta[2 * u] = x.x;
+    theta[2 * u + 1] = x.y;
   }
 }
 
-// ---------------------------------------------------------------------------
-// Segment loader: workgroup per (question i, 64-slot tile, kv head g).
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void load_segments_kernel(LoadSegmentsParams p, int tiles) {
-  __shared__ T s_v[kLoadTile][128 + 1];
-  const int g = blockIdx.y;
-  const int i = blockIdx.x / tiles;
-  const int tile = blockIdx.x - i * tiles;
-  const int n = p.init_len[i];
-  if (n < 0 || n > p.seg_cap) {
-    if (threadIdx.x == 0 && tile == 0 && g == 0) raise_flag(p.err_flag, kFlagBadLayout);
+template <typename T, int D>
+__device__ __forceinline__ void load_octet(const OctetArgs<T>& a, const double (&theta)[8]) {
+  typedef typename Oct<T>::type vec_t;
+  constexpr int half = D / 2, P = half / 8;         // pieces of 8 pairs per row
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t row = static_cast<int64_t>(a.Hkv) * D;
+  if (wave < 2) {
+    constexpr int HPW = 64 / (8 * P);                // heads a wave holds at a time
+    const int hs = lane / (8 * P), t = lane / P % 8, j0 = (lane % P) * 8;
+    if (t >= a.n) return;
+    const T* src = a.k_raw + (a.src_row + t) * row + j0;
+    T* dst = a.k + (a.head0 + a.tok + t) * D + j0;
+    float cs[8], sn[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rope_cos_sin(a.pos + t, theta[u], cs[u], sn[u]);
+#pragma unroll 4
+    for (int g = wave * HPW + hs; g < a.Hkv; g += 2 * HPW) {
+      const vec_t lo = *reinterpret_cast<const vec_t*>(src + g * D);
+      const vec_t hi = *reinterpret_cast<const vec_t*>(src + g * D + half);
+      vec_t x, y;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        float xr, yr;
+        rope_rotate(to_f32<T>(lo[u]), to_f32<T>(hi[u]), cs[u], sn[u], xr, yr);
+        x[u] = from_f32<T>(xr);
+        y[u] = from_f32<T>(yr);
+      }
+      T* d = dst + g * a.region * D;
+      *reinterpret_cast<vec_t*>(d) = x;
+      *reinterpret_cast<vec_t*>(d + half) = y;
+    }
     return;
   }
-  const int b = prompt_of(p.q_start, p.B, i);
-  if (threadIdx.x == 0 && tile == 0 && g == 0) p.seg_len[i] = n;
-  const int t0 = tile * kLoadTile;
-  if (t0 >= n) return;
-  const int nt = min(kLoadTile, n - t0);
-  const int D = p.D, half = D / 2;
-  const int64_t base_pos = instr_pos_base(p.instr_start, p.instr_len, p.S, b) + p.ctx_len[b];
-  const T* __restrict__ kr = static_cast<const T*>(p.k_raw);
-  const T* __restrict__ vr = static_cast<const T*>(p.v_raw);
-  T* __restrict__ sk = static_cast<T*>(p.seg_k);
-  T* __restrict__ svt = static_cast<T*>(p.seg_vt);
-  for (int e = threadIdx.x; e < nt * half; e += blockDim.x) {
-    const int tt = e / half, j = e - tt * half;
-    const int t = t0 + tt;
-    float c, sn;
-    rope_cos_sin(base_pos + t, p.inv_freq[j], c, sn);
-    const int64_t src = ((static_cast<int64_t>(i) * p.seg_cap + t) * p.Hkv + g) * D;
-    const int64_t dst = ((static_cast<int64_t>(i) * p.Hkv + g) * p.seg_cap + t) * D;
-    float x, y;
-    rope_rotate(to_f32<T>(kr[src + j]), to_f32<T>(kr[src + j + half]), c, sn, x, y);
-    sk[dst + j] = from_f32<T>(x);
-    sk[dst + j + half] = from_f32<T>(y);
+  for (int e = (wave - 2) * 64 + lane; e < a.Hkv * (D / 8); e += 128) {
+    const int g = e / (D / 8), d0 = (e % (D / 8)) * 8;
+    const T* src = a.v_raw + a.src_row * row + g * D + d0;
+    T* dst = a.vt + (a.head0 + g * a.region + a.tok) * D + d0 * 8;
+    vec_t v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) v[t] = *reinterpret_cast<const vec_t*>(src + min(t, a.n - 1) * row);
+    if (a.n == 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        vec_t w;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) w[t] = v[t][u];
+        *reinterpret_cast<vec_t*>(dst + u * 8) = w;
+      }
+    } else {                                         // tokens past the end are not the call's to write
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+          if (t < a.n) dst[u * 8 + t] = v[t][u];
+    }
   }
-  for (int e = threadIdx.x; e < nt * D; e += blockDim.x) {
-    const int tt = e / D, d = e - tt * D;
-    s_v[tt][d] = vr[((static_cast<int64_t>(i) * p.seg_cap + t0 + tt) * p.Hkv + g) * D + d];
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void load_context_kernel(LoadContextParams p, int blocks, int per) {
+  const int b = blockIdx.x / blocks;
+  const int blk = blockIdx.x - b * blocks;
+  const int64_t off = p.ctx_off[b];
+  const int len = p.ctx_len[b];
+  double theta[8];
+  octet_theta<D>(theta, p.inv_freq);
+  if (off < 0 || (off & 7) || len < 0 || len > p.max_ctx_len || off + len > p.pool) {
+    if (threadIdx.x == 0 && blk == 0) raise_flag(p.err_flag, kFlagBadLayout);
+    return;
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < nt * D; e += blockDim.x) {
-    const int d = e / nt, tt = e - d * nt;
-    svt[vt_index(static_cast<int64_t>(i) * p.Hkv + g, p.seg_cap, D, t0 + tt, d)] = s_v[tt][d];
+  const int64_t base = instr_pos_base(p.instr_start, p.instr_len, p.S, b);
+  for (int t0 = 8 * per * blk; t0 < min(8 * per * (blk + 1), len); t0 += 8) {
+    const OctetArgs<T> a = {static_cast<const T*>(p.k_raw), static_cast<const T*>(p.v_raw), static_cast<T*>(p.ctx_k),
+                            static_cast<T*>(p.ctx_vt), off + t0, 0, p.pool, off + t0, base + t0,
+                            min(8, len - t0), p.Hkv};
+    load_octet<T, D>(a, theta);
+  }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void load_segments_kernel(LoadSegmentsParams p, int blocks, int per) {
+  const int i = blockIdx.x / blocks;
+  const int blk = blockIdx.x - i * blocks;
+  const int lane = threadIdx.x & 63;
+  // the question's length, its angles' frequencies and the first 64 prompts'
+  // question ends and context lengths, in one round trip (a search of q_start
+  // load by load made this small kernel 26 us)
+  const int bl0 = lane < p.B ? lane : p.B - 1;
+  const int q10 = p.q_start[bl0 + 1], cl0 = p.ctx_len[bl0];
+  const int n = p.init_len[i];
+  double theta[8];
+  octet_theta<D>(theta, p.inv_freq);
+  if (n < 0 || n > p.seg_cap) {
+    if (threadIdx.x == 0 && blk == 0) raise_flag(p.err_flag, kFlagBadLayout);
+    return;
+  }
+  if (threadIdx.x == 0 && blk == 0) p.seg_len[i] = n;
+  if (8 * per * blk >= n) return;
+  // the prompt holding question i: the number of prompts whose questions all precede it
+  int k = __popcll(__ballot(lane < p.B && q10 <= i));
+  int b = k, len = __shfl(cl0, k < 64 ? k : 63, 64);
+  for (int b0 = 64; k == 64 && b0 < p.B; b0 += 64) {
+    const int bb = b0 + lane, bl = bb < p.B ? bb : p.B - 1;
+    const int q1 = p.q_start[bl + 1], cl = p.ctx_len[bl];
+    k = __popcll(__ballot(bb < p.B && q1 <= i));
+    b = b0 + k;
+    len = __shfl(cl, k < 64 ? k : 63, 64);
+  }
+  if (b >= p.B) {                                  // i past the last prompt's questions
+    b = p.B - 1;
+    len = p.ctx_len[b];
+  }
+  const int64_t base = instr_pos_base(p.instr_start, p.instr_len, p.S, b) + len;
+  for (int t0 = 8 * per * blk; t0 < min(8 * per * (blk + 1), n); t0 += 8) {
+    const OctetArgs<T> a = {static_cast<const T*>(p.k_raw), static_cast<const T*>(p.v_raw), static_cast<T*>(p.seg_k),
+                            static_cast<T*>(p.seg_vt), static_cast<int64_t>(i) * p.seg_cap + t0,
+                            static_cast<int64_t>(i) * p.Hkv * p.seg_cap, p.seg_cap, t0, base + t0, min(8, n - t0),
+                            p.Hkv};
+    load_octet<T, D>(a, theta);
   }
 }
 
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
+// Octets per workgroup: one, unless the workgroups of all ranges (n ranges
+// of `octets`) would exceed 2^22 (a launch holds fewer than 2^32 threads).
+static int octets_per_block(int64_t n, int octets) {
+  int per = 1;
+  while (n * ((octets + per - 1) / per) > (1 << 22) && per < octets) per *= 2;
+  return per;
+}
+
 hipError_t launch_load_context(int dtype, const LoadContextParams& p, hipStream_t s) {
-  const int tiles = (p.max_ctx_len + kLoadTile - 1) / kLoadTile;
-  if (tiles == 0 || p.B == 0) return hipSuccess;
-  dim3 grid(static_cast<unsigned>(p.B) * tiles, p.Hkv);
-  if (dtype == 0) load_context_kernel<float><<<grid, 256, 0, s>>>(p, tiles);
-  else load_context_kernel<uint16_t><<<grid, 256, 0, s>>>(p, tiles);
+  const int octets = p.max_ctx_len / 8 + (p.max_ctx_len % 8 != 0);
+  if (octets == 0 || p.B == 0) return hipSuccess;
+  const int per = octets_per_block(p.B, octets), blocks = (octets + per - 1) / per;
+  const unsigned grid = static_cast<unsigned>(p.B) * blocks;
+  if (dtype == 0 && p.D == 64) load_context_kernel<float, 64><<<grid, 256, 0, s>>>(p, blocks, per);
+  else if (dtype == 0) load_context_kernel<float, 128><<<grid, 256, 0, s>>>(p, blocks, per);
+  else if (p.D == 64) load_context_kernel<uint16_t, 64><<<grid, 256, 0, s>>>(p, blocks, per);
+  else load_context_kernel<uint16_t, 128><<<grid, 256, 0, s>>>(p, blocks, per);
   return hipGetLastError();
 }
 
 hipError_t launch_load_segments(int dtype, const LoadSegmentsParams& p, hipStream_t s) {
-  const int tiles = (p.seg_cap + kLoadTile - 1) / kLoadTile;
+  const int octets = p.seg_cap / 8;
   if (p.Nt == 0) return hipSuccess;
-  dim3 grid(static_cast<unsigned>(p.Nt) * tiles, p.Hkv);
-  if (dtype == 0) load_segments_kernel<float><<<grid, 256, 0, s>>>(p, tiles);
-  else load_segments_kernel<uint16_t><<<grid, 256, 0, s>>>(p, tiles);
+  const int per = octets_per_block(p.Nt, octets), blocks = (octets + per - 1) / per;
+  const unsigned grid = static_cast<unsigned>(p.Nt) * blocks;
+  if (dtype == 0 && p.D == 64) load_segments_kernel<float, 64><<<grid, 256, 0, s>>>(p, blocks, per);
+  else if (dtype == 0) load_segments_kernel<float, 128><<<grid, 256, 0, s>>>(p, blocks, per);
+  else if (p.D == 64) load_segments_kernel<uint16_t, 64><<<grid, 256, 0, s>>>(p, blocks, per);
+  else load_segments_kernel<uint16_t, 128><<<grid, 256, 0, s>>>(p, blocks, per);
   return hipGetLastError();
 }
 
