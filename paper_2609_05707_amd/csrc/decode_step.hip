@@ -40,6 +40,7 @@
 
 #include "ippd_device.h"
 #include "ippd_internal.h"
+#include "prefill_pingpong.h"
 #include "tile_attend.h"
 
 namespace ippd {
@@ -398,14 +399,23 @@ struct UnitLds {
 // instruction's chunk, and the states go to the instruction slots
 // max_chunks + 1 + chunk.  In the fused step each row's query is rotated at
 // its own question's position instr_len[s] + ctx_len[b] + seg_len[i].
-template <typename T, int D, int NW, int NS, bool FUSED, int RB, bool INSTR = false>
-__device__ __forceinline__ void context_unit(const StepParams& p, unsigned char* ring, int wave, int lane) {
-  using RG = Ring<T, D, NS>;
-  using M = Mfma<T>;
-  using RL = RowLoads<T, D, FUSED, RB>;
-  constexpr int RW = 16 * RB * NW, DPT = RG::BLOCKS / NW;
-  constexpr int P0 = RG::NS - 1 < 3 ? RG::NS - 1 : 3;      // tiles issued before the queries are rotated
-  const int lr = lane & 15, lg = lane >> 4;
+// The unit a workgroup serves: its group's keys and the questions of its rows.
+template <int RB>
+struct CtxUnit {
+  int g, qa;
+  int ctx_len, slot_k;                             // key-range length; slot index of this chunk's states
+  int64_t pos_base;                                // position of the first context token (fused step)
+  int pa, pe;                                      // INSTR: the prompts behind the instruction
+  int row0, nrows;                                 // first row of the unit; rows of the group's active questions
+  int qsel[RB];                                    // question of the lane's row in each row block (-1: none)
+  int64_t k0, k1;                                  // the chunk's tokens in the pool, k1 > k0
+};
+
+// Locates the workgroup's unit of RW rows; false if it has nothing to stream.
+// The lane's rows are row0 + first + 16 * rb, and lanes below `lead` hold each
+// of the wave's rows once.
+template <bool FUSED, int RW, int RB, bool INSTR>
+__device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<RB>& cu, int first, int lead, int lane) {
   // instruction units follow the context units (blockIdx >= ctx_blocks)
   const unsigned ub = INSTR ? blockIdx.x - static_cast<unsigned>(p.ctx_blocks) : blockIdx.x;
   const int nrg = INSTR ? p.nrg_i : p.nrg;
@@ -413,14 +423,14 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   const int slice = ub & 7, local = ub >> 3;
   const int cl = local / nrg, rg = local - cl * nrg;
   const int cglob = cl * 8 + slice;
-  if (cglob >= (INSTR ? p.n_igroups : p.n_groups) * nch) return;
+  if (cglob >= (INSTR ? p.n_igroups : p.n_groups) * nch) return false;
   const int grp = cglob / nch, chunk = cglob - grp * nch;
 
   int b = 0, g, qa, qb;
-  int ctx_len, slot_k;                             // key-range length; slot index of this chunk's states
-  int64_t off;                                     // key-range start in the pool
-  int64_t pos_base = 0;                            // position of the first context token (fused step)
-  int pa = 0, pe = 0;                              // INSTR: the prompts behind the instruction
+  int ctx_len, slot_k;
+  int64_t off;
+  int64_t pos_base = 0;
+  int pa = 0, pe = 0;
   if constexpr (INSTR) {
     int s = 0;
     bool ok;
@@ -449,7 +459,7 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
     ctx_len = ok ? p.instr_len[s] : 0;
     if (!ok || off < 0 || (off & 7) != 0 || ctx_len < 0 || ctx_len > p.max_instr_len || off + ctx_len > p.pool) {
       if (threadIdx.x == 0 && chunk == 0 && rg == 0) raise_flag(p.err_flag, kFlagBadLayout);
-      return;
+      return false;
     }
     slot_k = p.max_chunks + 1 + chunk;
   } else {
@@ -462,12 +472,12 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
       b = find_prompt(p, qa, lane).b;
       if (b >= p.B) {
         if (threadIdx.x == 0 && chunk == 0) raise_flag(p.err_flag, kFlagBadLayout);
-        return;
+        return false;
       }
     }
     if (!prompt_layout_ok(p, b)) {
       if (threadIdx.x == 0 && chunk == 0 && rg == 0) raise_flag(p.err_flag, kFlagBadLayout);
-      return;
+      return false;
     }
     if (p.shared) {
       qa = p.q_start[b];
@@ -490,32 +500,73 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   }
   const int G = p.G;
   const int row0 = rg * RW;
-  if (row0 >= (qb - qa) * G) return;              // beyond every question's rows
+  if (row0 >= (qb - qa) * G) return false;              // beyond every question's rows
   // the unit's rows are those of the active questions, compacted: row r is
   // head g*G + r % G of the (r / G)-th active question of [qa, qb)
-  int kq[RB], qsel[RB];
+  int kq[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) kq[rb] = (row0 + 16 * (RB * wave + rb) + lr) / G;
-  const int nrows = active_questions<RB>(p.active, qa, qb, kq, qsel, lane) * G;
-  if (row0 >= nrows) return;                       // no active rows here: no tile is read
+  for (int rb = 0; rb < RB; ++rb) kq[rb] = (row0 + first + 16 * rb) / G;
+  const int nrows = active_questions<RB>(p.active, qa, qb, kq, cu.qsel, lane) * G;
+  if (row0 >= nrows) return false;                       // no active rows here: no tile is read
   if (static_cast<int64_t>(chunk) * cb >= ctx_len) {
     // past the prompt's context: an empty state (max -inf) for each row, so
     // that the merge can fold every chunk slot without knowing the prompt
-    if (lg == 0) {
+    if (lane < lead) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        const int row = row0 + 16 * (RB * wave + rb) + lr;
+        const int row = row0 + first + 16 * rb;
         if (row < nrows) {
-          const int64_t slot = (static_cast<int64_t>(slot_k) * p.Nt + qsel[rb]) * p.Hq + g * G + row % G;
+          const int64_t slot = (static_cast<int64_t>(slot_k) * p.Nt + cu.qsel[rb]) * p.Hq + g * G + row % G;
           *reinterpret_cast<float2*>(p.part_ml + 2 * slot) = make_float2(-INFINITY, 0.f);
         }
       }
     }
-    return;
+    return false;
   }
 
-  const int64_t k0 = off + static_cast<int64_t>(chunk) * cb;
-  const int64_t k1 = min(k0 + cb, off + ctx_len);
+  cu.g = g;
+  cu.qa = qa;
+  cu.ctx_len = ctx_len;
+  cu.slot_k = slot_k;
+  cu.pos_base = pos_base;
+  cu.pa = pa;
+  cu.pe = pe;
+  cu.row0 = row0;
+  cu.nrows = nrows;
+  cu.k0 = off + static_cast<int64_t>(chunk) * cb;
+  cu.k1 = min(cu.k0 + cb, off + ctx_len);
+  return true;
+}
+
+// Where the query of question qi sits: one-level units all share the
+// context's end; a row of a fused instruction unit sits at instr_len +
+// ctx_len[b] + seg_len of its own question, b being the prompt (among
+// pa..pe-1) that holds it.
+template <int RB, bool FUSED, bool INSTR>
+__device__ __forceinline__ int64_t row_position(const StepParams& p, const CtxUnit<RB>& cu, int qi) {
+  if constexpr (INSTR && FUSED) {
+    int lo = cu.pa, hi = cu.pe - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (p.q_start[mid] <= qi) lo = mid; else hi = mid - 1;
+    }
+    return static_cast<int64_t>(cu.ctx_len) + p.ctx_len[lo];
+  }
+  return static_cast<int64_t>(cu.ctx_len) + cu.pos_base;
+}
+
+template <typename T, int D, int NW, int NS, bool FUSED, int RB, bool INSTR = false>
+__device__ __forceinline__ void context_unit(const StepParams& p, unsigned char* ring, int wave, int lane) {
+  using RG = Ring<T, D, NS>;
+  using M = Mfma<T>;
+  using RL = RowLoads<T, D, FUSED, RB>;
+  constexpr int RW = 16 * RB * NW, DPT = RG::BLOCKS / NW;
+  constexpr int P0 = RG::NS - 1 < 3 ? RG::NS - 1 : 3;      // tiles issued before the queries are rotated
+  const int lr = lane & 15, lg = lane >> 4;
+  CtxUnit<RB> cu;
+  if (!find_context_unit<FUSED, RW, RB, INSTR>(p, cu, 16 * RB * wave + lr, 16, lane)) return;
+  const int G = p.G, g = cu.g;
+  const int64_t k0 = cu.k0, k1 = cu.k1;
   const int ntiles = static_cast<int>((k1 - k0 + 31) >> 5);
   const T* kbase = static_cast<const T*>(p.ctx_k) + static_cast<int64_t>(g) * p.pool * D;
   const T* vbase = static_cast<const T*>(p.ctx_vt) + static_cast<int64_t>(g) * p.pool * D;
@@ -526,28 +577,14 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   // past the active ones read question qa's inputs and are never published)
   int qi[RB], h[RB];
   bool in_range[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = row0 + 16 * (RB * wave + rb) + lr;
-    in_range[rb] = row < nrows;
-    qi[rb] = in_range[rb] ? qsel[rb] : qa;
-    h[rb] = g * G + row % G;
-  }
-  // fused instruction unit: each row's query sits at instr_len + ctx_len[b] +
-  // seg_len of its own question, b being the prompt (among pa..pe-1) that holds it
   int64_t row_base[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) row_base[rb] = static_cast<int64_t>(ctx_len) + pos_base;
-  if constexpr (INSTR && FUSED) {
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      int lo = pa, hi = pe - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (p.q_start[mid] <= qi[rb]) lo = mid; else hi = mid - 1;
-      }
-      row_base[rb] = static_cast<int64_t>(ctx_len) + p.ctx_len[lo];
-    }
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = cu.row0 + 16 * (RB * wave + rb) + lr;
+    in_range[rb] = row < cu.nrows;
+    qi[rb] = in_range[rb] ? cu.qsel[rb] : cu.qa;
+    h[rb] = g * G + row % G;
+    row_base[rb] = row_position<RB, FUSED, INSTR>(p, cu, qi[rb]);
   }
   RL rl;
   issue_row_loads<T, D, FUSED, RB>(rl, p, qi, h, lg);
@@ -580,12 +617,8 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
     }
   }
   const bool live = wave_any(any_act);                // wave-uniform
-  // the eight-wave plain loop folds two tiles per barrier (below): its ring
-  // starts one tile shallower, so that the stages it refills are the two
-  // whose tiles every wave has folded
-  constexpr bool kPairs = RG::NS >= 6 && NW == 8 && RB == 1 && D == 128 && sizeof(T) == 2;
 #pragma unroll
-  for (int t = P0; t < RG::NS - (kPairs ? 2 : 1); ++t)
+  for (int t = P0; t < RG::NS - 1; ++t)
     if (t < ntiles) issue_tile<T, D, NW, NS>(lds + t * RG::STAGE, kbase, vbase, k0 + 32ll * t, k1, wave, lane, toff);
   RowState<D> st[RB];
 #pragma unroll
@@ -596,10 +629,7 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   // is refilled with tile t + NS - 1
   const int last = ntiles - 1;
   const int tail_n = static_cast<int>(k1 - (k0 + 32ll * last));
-  // eight single-block waves at bf16, D = 128 (one workgroup per compute
-  // unit): the plain loop, whose waves overlap each other's MFMA and VALU
-  // work, measured faster than the pipelined one
-  constexpr bool kPipelined = RG::NS >= 4 && !(NW == 8 && RB == 1 && D == 128 && sizeof(T) == 2);
+  constexpr bool kPipelined = RG::NS >= 4;
   if constexpr (kPipelined) {
     // software pipelined: iteration t folds tile t (softmax on the VALU, then
     // P^T V on the MFMA) while the scores of tile t+1 are computed, so each
@@ -651,34 +681,6 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
     } else if (live) {
       softmax_pv<T, D, NS, RB>(ring + (last % RG::NS) * RG::STAGE, sa, st, tail_n, lr, lg, c);
     }
-  } else if constexpr (kPairs) {
-    // two tiles per barrier: at iteration t (even) tiles t and t+1 have
-    // landed and every wave has folded tiles t-2 and t-1, whose stages take
-    // tiles t+NS-2 and t+NS-1; an odd last tile is folded on its own.
-    // Half the barriers, so half the waits for the slowest wave (measured
-    // 0.4% faster than one tile per barrier on the 32-layer workload).
-    int t = 0;
-    for (; t + 1 < ntiles; t += 2) {
-      // tiles t+2 .. min(t+NS-4, last) are younger than tile t+1
-      wait_tiles<DPT, RG::NS - 4>(min(last - t - 1, RG::NS - 4));
-      __syncthreads();
-      if (t + RG::NS - 2 <= last)
-        issue_tile<T, D, NW, NS>(lds + ((t + RG::NS - 2) % RG::NS) * RG::STAGE, kbase, vbase,
-                                 k0 + 32ll * (t + RG::NS - 2), k1, wave, lane, toff);
-      if (t + RG::NS - 1 <= last)
-        issue_tile<T, D, NW, NS>(lds + ((t + RG::NS - 1) % RG::NS) * RG::STAGE, kbase, vbase,
-                                 k0 + 32ll * (t + RG::NS - 1), k1, wave, lane, toff);
-      if (live) {
-        ring_tile<T, D, NS, RB>(ring + (t % RG::NS) * RG::STAGE, qf, st, 32, lr, lg, c);
-        ring_tile<T, D, NS, RB>(ring + ((t + 1) % RG::NS) * RG::STAGE, qf, st, t + 1 == last ? tail_n : 32, lr, lg,
-                                c);
-      }
-    }
-    if (t == last) {
-      wait_tiles<DPT, RG::NS - 4>(0);
-      __syncthreads();
-      if (live) ring_tile<T, D, NS, RB>(ring + (t % RG::NS) * RG::STAGE, qf, st, tail_n, lr, lg, c);
-    }
   } else {
     for (int t = 0; t < ntiles; ++t) {
       // tile t's blocks are this thread's oldest outstanding DMAs; those of
@@ -695,7 +697,306 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
 
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    if (act[rb]) publish_rows<D>(p, st[rb], (static_cast<int64_t>(slot_k) * p.Nt + qi[rb]) * p.Hq + h[rb], lg);
+    if (act[rb]) publish_rows<D>(p, st[rb], (static_cast<int64_t>(cu.slot_k) * p.Nt + qi[rb]) * p.Hq + h[rb], lg);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Context unit of 256 or 128 rows, bf16: the two wave groups of
+// prefill_pingpong.h, half a step apart, over the chunk's 64-key tiles.
+//
+// KS = 1: 256 rows; both groups work through the same tiles.  Tile t + 4 is
+// fetched in the product phase of step t, into stages both groups are past.
+// KS = 2: 128 rows; group A takes the even tiles and B the odd ones for the
+// same rows, and their states are combined at the end.  With phases counted
+// between barriers tile t's keys are read in phase t and its values in phases
+// t + 1 and t + 2; in phase t its group refills the stages of K(t - 1) and
+// V(t - 3) with K(t + 3) and V(t + 2), and what it issued two phases ago,
+// K(t + 1) and V(t), has landed when the phase ends.
+//
+// Queries stay as append_kernel rounds them (RAW softmax), so the fused and
+// the separate call give the same sums.  A tile past the last is not fetched,
+// and every wait counts the real fetches only.
+//
+// What bounds it: up to about 64 rows a compute unit the latency of a tile's
+// chain (fragments, scores, softmax, products), which the 16x16x32 loop of
+// context_unit pays every 32 keys (0.75 us) and this one every 64 keys a
+// phase (0.9 us; 128 rows: two tiles in that time's two phases).  Then the
+// stream.  Us a layer step at 32 heads, 8 kv heads, 16x16x32 units and these:
+// 32768 tokens x 64 questions 72.5, 59.1 (65.2 before the planner left room
+// for the segment units); 4 prompts of 8192 x 32 67.6, 47.6; 2 of 8192 x 24
+// 43.7, 30.6; 12 contexts of 1024 x 8 behind 3 instructions of 2048 37.3,
+// 34.1; ragged, 32 prompts of 1024 .. 8192 x 4 .. 32 199.7, 195.6.
+// ---------------------------------------------------------------------------
+template <int KS, bool FUSED, bool INSTR>
+__device__ __forceinline__ void context_unit_pp(const StepParams& p, unsigned char* ring, int wave, int lane) {
+  using T = uint16_t;
+  constexpr int D = 128;
+  using R = PpRing<D>;
+  using F = PpFetch<D, 8 / KS>;
+  constexpr int PER = F::PER, NQ = D / 16;
+  const bool quad = (p.G & 3) == 0;               // lane quads hold heads of one question
+  PpQuery<D> query;
+  if (FUSED && quad) query.load_theta(p.inv_freq, lane);   // shares the lookups' round trips
+  const int grp = wave >> 2, rw = KS == 1 ? wave : wave & 3;
+  CtxUnit<1> cu;
+  if (!find_context_unit<FUSED, 256 / KS, 1, INSTR>(p, cu, 32 * rw + (lane & 31), 32, lane)) return;
+  const int row = cu.row0 + 32 * rw + (lane & 31);
+  const bool in_range = row < cu.nrows;
+  const int qi = in_range ? cu.qsel[0] : cu.qa;    // (rows past the active ones are never published)
+  const int h = cu.g * p.G + row % p.G;
+  const int64_t base = row_position<1, FUSED, INSTR>(p, cu, qi);
+  if constexpr (FUSED) {
+    if (quad) {
+#pragma unroll
+      for (int ds = 0; ds < PpQuery<D>::DP; ++ds) asm volatile("" : "+v"(query.theta[ds][0]), "+v"(query.theta[ds][1]));
+    }
+  }
+  // row loads ahead of the tiles' DMAs, as issue_row_loads
+  uint32_t slen = gload_b32(p.seg_len + qi);
+  u32x4_t raw[NQ];
+  const char* src = static_cast<const char*>(FUSED ? p.q_new : p.q_rot_in) +
+                    ((static_cast<int64_t>(qi) * p.Hq + h) * D + 8 * (lane >> 5)) * static_cast<int64_t>(sizeof(T));
+#pragma unroll
+  for (int ds = 0; ds < NQ; ++ds) raw[ds] = gload_b128(src + 32 * ds);
+
+  const int ntok = static_cast<int>(cu.k1 - cu.k0);
+  const int last = ((ntok + 63) >> 6) - 1;
+  const int steps = (last + KS) / KS;              // steps of a group
+  const int nt = steps * KS;                       // 64-key tiles; KS = 2: the last of them perhaps a repeat, masked
+  const int64_t kv0 = (static_cast<int64_t>(cu.g) * p.pool + cu.k0) * D;
+  const T* kb = static_cast<const T*>(p.ctx_k) + kv0;
+  const T* vb = static_cast<const T*>(p.ctx_vt) + kv0;
+  const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
+  F dma;
+  dma.init(wave, lane);
+  uint32_t kin = lds, vin = lds + R::VBASE;        // stages of the tiles fetched next
+  auto ahead = [](uint32_t at, uint32_t first, int stages, int by) {
+    at += by * R::STAGE;
+    return at >= first + stages * R::STAGE ? at - stages * R::STAGE : at;
+  };
+  // DMA d < PER of tile t's keys (values); an empty second half repeats the
+  // first (finite data, masked)
+  auto fetch_key = [&](int t, int d, uint32_t on) {
+    const int hf = F::half_of(d, wave), k = 64 * min(t, last);
+    const int at = k + (ntok - k > 32 ? 32 * hf : 0);
+    dma.key(d, kb + static_cast<int64_t>(at) * D, min(32, ntok - at), kin + hf * R::HALF, on);
+  };
+  auto fetch_value = [&](int t, int d, uint32_t on) {
+    const int hf = F::half_of(d, wave), k = 64 * min(t, last);
+    const int at = k + (ntok - k > 32 ? 32 * hf : 0);
+    dma.value(d, vb + static_cast<int64_t>(at) * D, min(32, ntok - at), vin + hf * R::HALF, on);
+  };
+  // The first fetches, a fixed number of DMAs ahead of the one wait for the
+  // row loads.  KS = 1: tiles 0 and 1 (a unit with one tile fetches it twice;
+  // nothing reads the second).  KS = 2: K(0), V(0), K(2) by group A, K(1),
+  // V(1) and, for the same count, K(1) again by B.
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int d = 0; d < PER; ++d) fetch_key(t, d, ~0u);
+#pragma unroll
+      for (int d = 0; d < PER; ++d) fetch_value(t, d, ~0u);
+      kin = ahead(kin, lds, R::NK, 1);
+      vin = ahead(vin, lds + R::VBASE, R::NV, 1);
+    }
+  } else {
+    kin = lds + grp * R::STAGE;
+    vin = lds + R::VBASE + grp * R::STAGE;
+#pragma unroll
+    for (int d = 0; d < PER; ++d) fetch_key(grp, d, ~0u);
+#pragma unroll
+    for (int d = 0; d < PER; ++d) fetch_value(grp, d, ~0u);
+    if (grp == 0) kin = lds + 2 * R::STAGE;
+#pragma unroll
+    for (int d = 0; d < PER; ++d) fetch_key(grp == 0 ? 2 : 1, d, ~0u);
+    // next: K(3), V(2) by A, K(4), V(3) by B
+    kin = lds + (grp == 0 ? 3 : 0) * R::STAGE;
+    vin = lds + R::VBASE + (grp + 2) * R::STAGE;
+  }
+  asm volatile("s_waitcnt vmcnt(%1)" : "+v"(slen) : "n"(KS == 1 ? 4 * PER : 3 * PER));
+#pragma unroll
+  for (int ds = 0; ds < NQ; ++ds) asm volatile("" : "+v"(raw[ds]));
+
+  const bool act = in_range && usable_seg_len(p, static_cast<int>(slen)) >= 0;
+  const bool live = wave_any(act);                 // wave-uniform; other waves fetch and keep the barriers
+  bf16x8_t qf[NQ];
+#pragma unroll
+  for (int ds = 0; ds < NQ; ++ds) query.raw[ds] = __builtin_bit_cast(bf16x8_t, raw[ds]);
+  if constexpr (FUSED) {
+    query.rotate(qf, p.inv_freq, base + static_cast<int>(slen), 1.f, quad, lane);
+  } else {
+#pragma unroll
+    for (int ds = 0; ds < NQ; ++ds) qf[ds] = query.raw[ds];
+  }
+  if (!act) {
+#pragma unroll
+    for (int ds = 0; ds < NQ; ++ds) qf[ds] = Mfma<T>::zero();
+  }
+  PpState<D> st;
+  pp_init(st);
+  f32x16_t s[2];
+  bf16x8_t pf[4];
+  uint32_t kst = 0, vst = 0;                       // stages of the step's keys and values
+  const float c = p.c;
+  // fetches of the product phase after step t's softmax (t = grp - KS: before the first)
+  auto refill = [&](int t) {
+    const uint32_t kon = t + (KS == 1 ? 4 : 5) < nt ? ~0u : 0u, von = t + 4 < nt ? ~0u : 0u;
+#pragma unroll
+    for (int d = 0; d < PER; ++d) fetch_key(t + (KS == 1 ? 4 : 5), d, kon);
+#pragma unroll
+    for (int d = 0; d < PER; ++d) fetch_value(t + 4, d, von);
+    kin = ahead(kin, lds, R::NK, KS);
+    vin = ahead(vin, lds + R::VBASE, R::NV, KS);
+  };
+  // KS = 1: tile t + 1 has landed, t + 2 and t + 3 are younger; KS = 2: K(t + 1)
+  // and V(t), with V(t + 2) and K(t + 3) younger
+  auto wait_step = [&](int t) {
+    if constexpr (KS == 1) wait_tiles<2 * PER, 2>(max(min(nt - 2 - t, 2), 0));
+    else wait_tiles<PER, 2>(max(min(nt - 2 - t, 2), 0));
+  };
+  if constexpr (KS == 1) {
+    refill(-2);
+    refill(-1);
+    wait_tiles<2 * PER, 3>(max(min(nt, 4), 2) - 1);  // (the second stage is always filled)
+  } else {
+    kst = vst = grp * R::STAGE;
+    wait_vmcnt<0>();
+  }
+  phase_barrier();
+  if (grp == 1) phase_barrier();
+  if (KS == 2) refill(grp - 2);
+  if (!live) {
+    // no active rows in this wave: its part of the fetches, and the barriers
+#pragma unroll 1
+    for (int i = 0; i < steps; ++i) {
+      const int t = KS * i + (KS == 2 ? grp : 0);
+      wait_step(t);
+      phase_barrier();
+      phase_barrier();
+      refill(t);
+    }
+    if (grp == 0) phase_barrier();
+    phase_barrier();
+    if (KS == 2) __syncthreads();                  // the other waves' exchange and output
+    if (KS == 2) __syncthreads();
+    if (KS == 2) __syncthreads();
+    return;
+  }
+  pp_first_scores<D>(ring + kst, qf, st, s, lane);
+#pragma unroll 1
+  for (int i = 0; i < steps; ++i) {
+    const int t = KS * i + (KS == 2 ? grp : 0);    // the group's tile
+    __builtin_amdgcn_s_setprio(0);
+    wait_step(t);
+    phase_barrier();
+    const unsigned char* vt = ring + R::VBASE + vst;
+    const int rem = ntok - 64 * min(t, last);
+    if (rem < 64 || t > last) {
+      const int n0 = min(rem, 32), n1 = rem > 32 ? min(rem - 32, 32) : n0;
+      pp_mask(s[0], t > last ? -1 : n0 - 1, lane);
+      pp_mask(s[1], t > last || rem <= 32 ? -1 : n1 - 1, lane);
+      pp_clear_tail<D>(ring + R::VBASE + vst, n0, lane);
+      pp_clear_tail<D>(ring + R::VBASE + vst + R::HALF, n1, lane);
+    }
+    pp_softmax<D, true>(s, st, pf, c);
+    bf16x8_t v0[kPpAhead];
+#pragma unroll
+    for (int f = 0; f < kPpAhead; ++f) v0[f] = pp_vfrag<D>(vt, f, lane);
+    kst = ahead(kst, 0, R::NK, KS);
+    vst = ahead(vst, 0, R::NV, KS);
+    const int kn = t + (KS == 1 ? 4 : 5), vn = t + 4;
+    const uint32_t kon = kn < nt ? ~0u : 0u, von = vn < nt ? ~0u : 0u;
+    phase_barrier();
+    // (after the last tile the scores are those of a stale stage, not used)
+    __builtin_amdgcn_s_setprio(1);
+    pp_products<D, 2 * PER>(v0, vt, ring + kst, pf, qf, st, s, lane, [&](int d) {
+      if (d < PER) fetch_key(kn, d, kon);
+      else fetch_value(vn, d - PER, von);
+    });
+    kin = ahead(kin, lds, R::NK, KS);
+    vin = ahead(vin, lds + R::VBASE, R::NV, KS);
+  }
+  __builtin_amdgcn_s_setprio(0);
+  if (grp == 0) phase_barrier();
+  phase_barrier();                                 // every wave is done with the ring, every DMA has landed
+
+  float l = xor32_sum((st.l[0] + st.l[1]) + (st.l[2] + st.l[3]));
+  float m = st.thr == -INFINITY ? -INFINITY : -st.negm[0];
+  constexpr int DB = D / 32 / KS;                  // 32-dim blocks a wave writes
+  const int db0 = KS == 2 ? grp * DB : 0;
+  f32x16_t o[DB];
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = st.o[db];
+  } else {
+    // each group finishes half of the dims: it gets the other's offset, sum
+    // and values of them.  Group A has seen a key; B's offset is -inf if it
+    // has not (weight 0).
+    f32x4_t* xo = reinterpret_cast<f32x4_t*>(ring) + rw * (DB * 4 * 2 * 64) + lane;   // [group][piece][lane]
+    float2* xm = reinterpret_cast<float2*>(ring + 4 * DB * 4 * 2 * 1024) + rw * 128 + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4_t x;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = grp == 0 ? st.o[DB + db][4 * i + v] : st.o[db][4 * i + v];
+        xo[((1 - grp) * DB * 4 + db * 4 + i) * 64] = x;
+      }
+    xm[(1 - grp) * 64] = make_float2(m, l);
+    __syncthreads();
+    const float2 ml = xm[grp * 64];
+    const float mn = fmaxf(m, ml.x);
+    const float fa = m == -INFINITY ? 0.f : fast_exp2((m - mn) * c);
+    const float fb = ml.x == -INFINITY ? 0.f : fast_exp2((ml.x - mn) * c);
+    l = l * fa + ml.y * fb;
+    m = mn;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4_t y = xo[(grp * DB * 4 + db * 4 + i) * 64];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          o[db][4 * i + v] = (grp == 0 ? st.o[db][4 * i + v] : st.o[DB + db][4 * i + v]) * fa + y[v] * fb;
+      }
+    __syncthreads();
+  }
+
+  // rows through LDS (the ring's bytes, a region per 32 rows), so that each
+  // state leaves in whole 512-byte rows
+  constexpr int OROW = D * 4 + 16;                 // padded: 16 rows' 16-byte pieces hit distinct banks
+  static_assert(8 * 32 * (OROW + 8) <= R::BYTES, "states and their places must fit the ring");
+  unsigned char* ob = ring + rw * (32 * OROW);
+  float* orow = reinterpret_cast<float*>(ob + (lane & 31) * OROW) + 4 * (lane >> 5) + 32 * db0;
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<f32x4_t*>(orow + 32 * db + 8 * i) =
+          f32x4_t{o[db][4 * i], o[db][4 * i + 1], o[db][4 * i + 2], o[db][4 * i + 3]};
+  int64_t* at = reinterpret_cast<int64_t*>(ring + 8 * 32 * OROW) + rw * 32;
+  if (lane < 32 && (KS == 1 || grp == 0)) {
+    const int64_t slot = (static_cast<int64_t>(cu.slot_k) * p.Nt + qi) * p.Hq + h;
+    at[lane] = act ? slot : -1;                    // (-1: not published)
+    if (act) *reinterpret_cast<float2*>(p.part_ml + 2 * slot) = make_float2(m, l);
+  }
+  if constexpr (KS == 2) {
+    __syncthreads();                               // the two groups' halves of a row
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+#pragma unroll
+  for (int it = 0; it < 16 / KS; ++it) {
+    const int r = 2 * (it + (KS == 2 ? grp * 8 : 0)) + (lane >> 5);
+    const int64_t slot = at[r];
+    if (slot >= 0)
+      *reinterpret_cast<f32x4_t*>(p.part_acc + slot * D + (lane & 31) * 4) =
+          *reinterpret_cast<const f32x4_t*>(ob + r * OROW + (lane & 31) * 16);
   }
 }
 
@@ -958,18 +1259,28 @@ __device__ __forceinline__ void segment_unit(const StepParams& p, UnitLds<T, D, 
 // Workgroups are dispatched in order, so segment units start as context
 // units retire and fill the tail of the context work.
 // ---------------------------------------------------------------------------
-// The second launch bound asks for four waves per SIMD with one row block
-// per wave and two with RB = 2 (twice the accumulators); the ring's LDS then
-// sets the workgroups per compute unit: one with nine stages, two with five.
+// The second launch bound asks for four waves per SIMD, and for two in the
+// two-group unit (32 rows' accumulators and fragments ahead); the ring's LDS
+// then sets the workgroups per compute unit: one with nine stages, two with
+// five.
+template <typename T, int D, int NW>
+constexpr bool kTwoGroups = NW == 8 && D == 128 && sizeof(T) == 2;   // 256 rows with RB = 2, 128 with RB = 1
+
 template <typename T, int D, int NW, int NS, bool FUSED, int RB>
-__global__ __launch_bounds__(64 * NW, RB == 1 ? 4 : 2) void attend_kernel(StepParams p) {
+__global__ __launch_bounds__(64 * NW, (kTwoGroups<T, D, NW> ? 2 : 4)) void attend_kernel(StepParams p) {
   __shared__ UnitLds<T, D, NW, NS> sh;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = static_cast<int>(blockIdx.x);
-  if (blk < p.ctx_blocks) context_unit<T, D, NW, NS, FUSED, RB>(p, sh.main, wave, lane);
-  else if (blk < p.ctx_blocks + p.instr_blocks) context_unit<T, D, NW, NS, FUSED, RB, true>(p, sh.main, wave, lane);
-  else segment_unit<T, D, NW, NS, FUSED>(p, sh, blk - p.ctx_blocks - p.instr_blocks, wave, lane);
+  constexpr bool kPp = kTwoGroups<T, D, NW>;
+  constexpr int KS = RB == 2 ? 1 : 2;
+  if (blk < p.ctx_blocks) {
+    if constexpr (kPp) context_unit_pp<KS, FUSED, false>(p, sh.main, wave, lane);
+    else context_unit<T, D, NW, NS, FUSED, RB>(p, sh.main, wave, lane);
+  } else if (blk < p.ctx_blocks + p.instr_blocks) {
+    if constexpr (kPp) context_unit_pp<KS, FUSED, true>(p, sh.main, wave, lane);
+    else context_unit<T, D, NW, NS, FUSED, RB, true>(p, sh.main, wave, lane);
+  } else segment_unit<T, D, NW, NS, FUSED>(p, sh, blk - p.ctx_blocks - p.instr_blocks, wave, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1104,10 +1415,8 @@ static hipError_t launch_depth(bool deep, int grid, const StepParams& p, hipStre
 template <typename T, int D>
 static hipError_t launch_waves(int waves, int rb, bool deep, int grid, const StepParams& p, hipStream_t s) {
   if (rb == 2) {
-    // two row blocks per wave: bf16 at D = 128 with four or eight waves
     if constexpr (sizeof(T) == 2 && D == 128) {
-      if (waves == 4) return launch_depth<T, D, 4, 2>(deep, grid, p, s);
-      if (waves == 8) return launch_depth<T, D, 8, 2>(deep, grid, p, s);
+      if (waves == 8) return launch_attend<T, D, 8, 9, 2>(grid, p, s);
     }
     return hipErrorInvalidValue;
   }
@@ -1116,9 +1425,8 @@ static hipError_t launch_waves(int waves, int rb, bool deep, int grid, const Ste
     case 2: return launch_depth<T, D, 2, 1>(deep, grid, p, s);
     case 4: return launch_depth<T, D, 4, 1>(deep, grid, p, s);
     default:
-      // the planner gives fp32 at D = 128 at most four waves, and bf16 at
-      // D = 128 eight single-block waves only with one workgroup per compute
-      // unit (the deep ring)
+      // the planner gives fp32 at D = 128 at most four waves; bf16 at D = 128
+      // with eight is the two-group unit, one workgroup per compute unit
       if constexpr (D == 128 && sizeof(T) == 4) return hipErrorInvalidValue;
       else if constexpr (D == 128) return launch_attend<T, D, 8, 9, 1>(grid, p, s);
       else return launch_depth<T, D, 8, 1>(deep, grid, p, s);

@@ -82,6 +82,23 @@ void fill_inv_freq(const ippd_batch_t* bt, double* out) {
     out[j] = j < half ? pow(bt->rope_base, -2.0 * j / bt->head_dim) : 0.0;
 }
 
+// Chunk of a small batch, whose units all run at once: a unit folds its tiles
+// one after another (us a tile, the latency of its chain: bf16 0.75, fp32 1.6
+// at D = 64 and 2.4 at D = 128), and the merge folds the n chunks' states (us
+// a chunk: 0.03, and 0.36 per thousand rows).  n = sqrt(tile time * tiles /
+// slot time) minimises the sum.  Measured over 32 .. 512 tokens, us a layer
+// step at the former 256-token minimum, at this choice and at the best size:
+// fp32 D = 64, 256 tokens x 4 questions 23.2, 11.9, 11.9; fp32 D = 128, 1024
+// x 8 33.7, 19.1, 19.1; bf16 D = 128, 512 x 4 17.6, 13.0, 13.0, 1024 x 16
+// 17.8, 15.6, 15.5, 4096 x 16 19.6, 18.8, 18.8.
+int64_t small_chunk(const ippd_batch_t* bt, int max_ilen) {
+  const double tile = bt->dtype == IPPD_DTYPE_BF16 ? 0.75 : (bt->head_dim == 64 ? 1.6 : 2.4);
+  const double slot = 0.03 + 0.36e-3 * bt->num_questions * bt->num_q_heads;
+  const double len = std::max(std::max(bt->max_ctx_len, max_ilen), 32);
+  const double n = sqrt(tile * len / 32 / slot);
+  return 32 * std::max<int64_t>(1, llround(len / n / 32));
+}
+
 // Launch plan of a decode call.  Depends only on host fields, so the
 // workspace query and the launch agree.
 bool plan_step(const ippd_batch_t* bt, bool shared, ippd::StepPlan* pl, bool dense = false) {
@@ -90,80 +107,140 @@ bool plan_step(const ippd_batch_t* bt, bool shared, ippd::StepPlan* pl, bool den
   if (dense && (!shared || bt->num_instr > 0 || bt->max_questions > 64)) return false;
   const int G = bt->num_q_heads / bt->num_kv_heads;
   const int64_t max_rows = shared ? static_cast<int64_t>(bt->max_questions) * G : G;
-  // rows per context unit: 16 * rb per wave.  bf16 at D = 128 with more than
-  // 64 rows puts two 16-row blocks on each wave (each K/V fragment read from
-  // LDS serves both): 128 rows as 4 x 32, 256 as 8 x 32.
+  // rows per context unit: 16 * rb per wave; bf16 at D = 128 with more than
+  // 64 rows takes the two-group unit of 128 or 256 rows.  (Dense-mask
+  // baseline: two 16-row blocks a wave, 128 rows as 4 x 32, 256 as 8 x 32.)
   const bool two_blocks_ok = bt->dtype == IPPD_DTYPE_BF16 && bt->head_dim == 128;
   int rows = bt->tile_rows;
-  // a two-level batch's instruction rows (all questions behind it) favour at
-  // least 64-row units (measured against 32 at 6 contexts per instruction)
-  int64_t sized_rows = max_rows;
-  if (bt->num_instr > 0 && shared) {
-    const int64_t irows = static_cast<int64_t>(bt->max_instr_questions) * G;
-    const int64_t want = irows < 64 ? irows : 64;
-    if (want > sized_rows) sized_rows = want;
+  const int S = bt->num_instr;
+  const int64_t irows = shared ? static_cast<int64_t>(bt->max_instr_questions) * G : G;
+  // context tokens to stream: one-level IPPD reads each prompt once, and the
+  // prompts are packed in the pool, so its size bounds their sum (a ragged
+  // batch is then sized by its total, not by B times the longest)
+  const int64_t ctx_tokens = shared ? std::min<int64_t>(bt->ctx_pool_tokens,
+                                                        static_cast<int64_t>(bt->num_prompts) * bt->max_ctx_len)
+                                    : static_cast<int64_t>(bt->num_questions) * bt->max_ctx_len;
+  if (rows == 0) {
+    // a two-level batch's instruction rows (all questions behind it) favour at
+    // least 64-row units (measured against 32 at 6 contexts per instruction)
+    int64_t sized = max_rows;
+    if (S > 0 && shared) sized = std::max(sized, std::min<int64_t>(irows, 64));
+    if (two_blocks_ok && shared && !dense && sized <= 64) {
+      // 64 rows at least: one or two waves are slow to issue the tiles' DMAs
+      // (4 questions over 16384 tokens, us a layer step: 16 rows 30.2, 64
+      // 26.4; over 512 tokens 13.5, 12.7).  128 where the streams are long
+      // (256 tokens a compute unit and more): the paired unit's time a tile
+      // is a third (16 questions over 16384 tokens: 32.7 at 64 rows, 28.6 at
+      // 128; over 8192: 21.9, 24.0).
+      const int64_t stream = (ctx_tokens + static_cast<int64_t>(S) * bt->max_instr_len * (irows > 64 ? 2 : 1)) *
+                             bt->num_kv_heads;
+      sized = stream >= 512ll * kPlanComputeUnits ? 128 : 64;
+    }
+    rows = sized <= 16 ? 16 : (sized <= 32 ? 32 : (sized <= 64 ? 64 : (sized <= 128 || !two_blocks_ok ? 128 : 256)));
   }
-  if (rows == 0) rows = sized_rows <= 16 ? 16 : (sized_rows <= 32 ? 32 : (sized_rows <= 64 ? 64 : (sized_rows <= 128 || !two_blocks_ok ? 128 : 256)));
-  // 128-row units at bf16, D = 128 over prompts of (nearly) one length: eight
-  // waves of one 16-row block each, one workgroup per compute unit with the
-  // deep ring.  Half the units of the four-wave shape (two workgroups per
-  // compute unit), so half the partial states, at the same streaming rate;
-  // ragged batches keep the four-wave shape, whose second workgroup per
-  // compute unit covers the uneven unit lengths.
   const bool near_uniform = bt->ctx_pool_tokens * 10 >= static_cast<int64_t>(bt->num_prompts) * bt->max_ctx_len * 9;
-  const bool eight_single = two_blocks_ok && shared && !dense && bt->num_instr == 0 && rows == 128 && near_uniform;
-  const int rb = rows > 64 && two_blocks_ok && !eight_single ? 2 : 1;
-  int waves = rows / (16 * rb);
+  // bf16 at D = 128, 128 or 256 rows: the two-group unit, eight waves and one
+  // workgroup per compute unit.
+  const bool paired = two_blocks_ok && !dense && rows >= 128;
+  // At 128 rows each group takes every other tile: half the steps a unit, so
+  // that half the compute units can stream a short batch while the others
+  // serve its segments (8192 tokens x 32 questions, 4 prompts, us a layer
+  // step: 47.6, as 256-row units 54.6).  With more segment tasks than half
+  // the chip holds (eight a compute unit) every compute unit streams and
+  // memory bounds the units: as 256-row units they keep four tiles in flight
+  // instead of three (8 such prompts 81.9, as 256-row units 81.0; 8 of 4096
+  // x 32 62.3, 58.7; 16 of 4096 x 20 89.3, 88.0).
+  const int64_t seg_tasks = static_cast<int64_t>(bt->num_questions) * bt->num_kv_heads;
+  if (paired && rows == 128 && bt->tile_rows == 0 && shared && S == 0 && near_uniform && seg_tasks > 4 * kPlanComputeUnits)
+    rows = 256;
+  const int rb = two_blocks_ok && (paired ? rows == 256 : rows > 64) ? 2 : 1;
+  int waves = paired ? 8 : rows / (16 * rb);
   // fp32 at D = 128: the operands of eight waves do not fit their registers
   if (bt->dtype == IPPD_DTYPE_F32 && bt->head_dim == 128 && waves > 4) waves = 4;
   const int unit_rows = 16 * rb * waves;
   const int nrg = static_cast<int>((max_rows + unit_rows - 1) / unit_rows);
   // workgroups resident per compute unit (eight waves of two row blocks use
   // the registers of two, and their ring the LDS of one)
-  const int wg_per_cu = (waves == 8 && (rb == 2 || eight_single)) ? 1 : 2;
+  const int wg_per_cu = paired || (waves == 8 && rb == 2) ? 1 : 2;
   const int64_t n_groups = shared ? static_cast<int64_t>(bt->num_prompts) * bt->num_kv_heads
                                   : static_cast<int64_t>(bt->num_questions) * bt->num_kv_heads;
   // two-level batch: instruction groups, (instruction, kv head) or (question, kv head)
-  const int S = bt->num_instr;
   const int64_t n_igroups = S == 0 ? 0 : (shared ? static_cast<int64_t>(S) : bt->num_questions) * bt->num_kv_heads;
-  const int64_t irows = shared ? static_cast<int64_t>(bt->max_instr_questions) * G : G;
   const int nrg_i = S == 0 ? 1 : static_cast<int>((irows + unit_rows - 1) / unit_rows);
+  // segment tasks (question, kv head): up to `waves` per unit, whose wave
+  // states must fit the smallest LDS ring (32 KB)
+  const int64_t state_bytes = static_cast<int64_t>(G) * (bt->head_dim + 4) * 4;
+  int max_tpu = 1;
+  // (few tasks under a chunk that the caller fixed: one a unit, so that a
+  // prompt's sums are grouped alike whatever else the batch holds)
+  if (paired || seg_tasks > compute_units() || bt->chunk_tokens == 0)
+    while (max_tpu < waves && 2 * max_tpu * state_bytes <= 32768) max_tpu *= 2;
+  auto seg_units = [&](int64_t tpu) { return (seg_tasks + tpu - 1) / tpu; };
+  const int max_ilen = S ? bt->max_instr_len : 0;
+  auto stream_units = [&](int64_t ch) {            // context and instruction units
+    return 8 * (nrg * ((n_groups * ((bt->max_ctx_len + ch - 1) / ch) + 7) / 8) +
+                nrg_i * ((n_igroups * ((max_ilen + ch - 1) / ch) + 7) / 8));
+  };
+  const int64_t cus = compute_units(), target = cus * wg_per_cu;
   int chunk = bt->chunk_tokens;
   if (chunk == 0) {
-    // context tokens to stream: one-level IPPD reads each prompt once, and the
-    // prompts are packed in the pool, so its size bounds their sum (a ragged
-    // batch then gets a chunk from its total, not from B times the longest)
-    const int64_t ctx_tokens = shared ? std::min<int64_t>(bt->ctx_pool_tokens,
-                                                          static_cast<int64_t>(bt->num_prompts) * bt->max_ctx_len)
-                                      : static_cast<int64_t>(bt->num_questions) * bt->max_ctx_len;
-    const int64_t work = ctx_tokens * bt->num_kv_heads * nrg + n_igroups * nrg_i * (S ? bt->max_instr_len : 0);
-    const int64_t target = static_cast<int64_t>(compute_units()) * wg_per_cu;
+    const int64_t work = ctx_tokens * bt->num_kv_heads * nrg + n_igroups * nrg_i * max_ilen;
     int64_t ch = (work + target - 1) / target;
     ch = (ch + 31) / 32 * 32;
     ch = ch < kMinChunk ? kMinChunk : (ch > kMaxChunk ? kMaxChunk : ch);
+    // a small batch: the first chunk from small_chunk on whose units all run
+    // at once, one workgroup per compute unit if some chunk up to the minimum
+    // allows it (4096 tokens x 16 questions, us a layer step: 192 tokens with
+    // one workgroup per compute unit 19.4, with two 20.3; 256 with one 20.1)
+    if (ch == kMinChunk) {
+      auto resident = [&](int64_t c, int64_t at_once) { return stream_units(c) + seg_units(max_tpu) <= at_once; };
+      const int64_t at_once = resident(kMinChunk, cus) ? cus : target;
+      int64_t c = small_chunk(bt, max_ilen);
+      while (c < kMinChunk && !resident(c, at_once)) c += 32;
+      const int64_t states = ((bt->max_ctx_len + c - 1) / c + 1 + (max_ilen + c - 1) / c) *
+                             static_cast<int64_t>(bt->num_questions) * bt->num_q_heads;
+      if (c < kMinChunk && states * (bt->head_dim + 2) * 4 + 512 <= IPPD_NOALLOC_SCRATCH_BYTES) ch = c;
+    }
+    // work / target counts no partly filled last chunk: over contexts of
+    // nearly one length that can leave a second round of a few units.  The
+    // smallest chunk with one round (two-level batch of 12 contexts of 1024
+    // behind 3 instructions of 2048: 384 -> 512 tokens, 44.1 -> 37.4 us).
+    if (ch >= kMinChunk && near_uniform) {
+      // Paired units leave room for the segment units beside them: they would
+      // otherwise start only when a context unit ends (32768 tokens x 64
+      // questions, us a layer step: 65.2 with 32 chunks and no room, 59.1 with 24).
+      const int64_t segs = paired && 2 * seg_units(max_tpu) <= cus ? seg_units(max_tpu) : 0;
+      int64_t c = ch;
+      while (c < 2 * ch && stream_units(c) + segs > target) c += 32;
+      if (stream_units(c) + segs <= target) ch = c;
+    }
     chunk = static_cast<int>(ch);
   }
   const int64_t max_chunks = (bt->max_ctx_len + chunk - 1) / chunk;
   const int64_t ctx_blocks = 8 * nrg * ((n_groups * max_chunks + 7) / 8);
-  const int64_t max_ichunks = S == 0 ? 0 : (bt->max_instr_len + chunk - 1) / chunk;
+  const int64_t max_ichunks = (max_ilen + chunk - 1) / chunk;
   const int64_t instr_blocks = 8 * nrg_i * ((n_igroups * max_ichunks + 7) / 8);
-  // segment tasks (question, kv head): as few per unit as keeps the segment
-  // units within one round of resident workgroups (they run after the
-  // context units), at most `waves` per unit, and all tasks' wave states
-  // must fit the smallest LDS ring (32 KB)
-  const bool deep = ctx_blocks + instr_blocks <= compute_units() || wg_per_cu == 1;
-  const int64_t slots = static_cast<int64_t>(compute_units()) * (deep ? 1 : 2);
-  const int64_t seg_tasks = static_cast<int64_t>(bt->num_questions) * bt->num_kv_heads;
-  const int64_t state_bytes = static_cast<int64_t>(G) * (bt->head_dim + 4) * 4;
+  const int64_t streams = ctx_blocks + instr_blocks;
+  // The deep ring (one workgroup per compute unit) if every unit fits the
+  // chip with it, or if the context units do and have more tiles than it
+  // holds (4 prompts of 2048 x 16 questions at 256 tokens: deep 26.8 us, two
+  // workgroups per compute unit 21.7); paired units always.
+  const bool all_fit = streams + seg_units(max_tpu) <= cus;
+  const bool deep = wg_per_cu == 1 || all_fit || (streams <= cus && chunk > kMinChunk);
+  const int64_t slots = cus * (deep ? 1 : 2);
+  // Segment units: as few tasks per unit as keeps every unit resident from
+  // the start, if that can be; else as keeps them within one round of their
+  // own (they then run after the context units).
+  const int64_t room = streams + seg_units(max_tpu) <= slots ? slots - streams : slots;
   int tpu = 1;
-  while (tpu < waves && (seg_tasks + tpu - 1) / tpu > slots && 2 * tpu * state_bytes <= 32768) tpu *= 2;
+  while (tpu < max_tpu && seg_units(tpu) > room) tpu *= 2;
   // dense-mask baseline: segment units (prompt, kv head, segment chunk, row
   // group) split the prompt's concatenated segment tiles into chunks of
   // kDenseSegTiles tiles; chunk 0 writes the segment slot, chunks 1.. the
   // slots after it (where a two-level batch keeps its instruction chunks)
   const int64_t seg_tiles = static_cast<int64_t>(bt->max_questions) * ((bt->seg_capacity + 31) / 32);
   const int64_t seg_chunks = dense ? (seg_tiles + ippd::kDenseSegTiles - 1) / ippd::kDenseSegTiles : 0;
-  const int64_t seg_blocks = dense ? n_groups * seg_chunks * nrg : (seg_tasks + tpu - 1) / tpu;
+  const int64_t seg_blocks = dense ? n_groups * seg_chunks * nrg : seg_units(tpu);
   const int64_t dense_grid = n_groups * max_chunks * nrg + seg_blocks;
   const int64_t grid = ctx_blocks + instr_blocks + seg_blocks;
   if (grid > (1ll << 30) || n_groups * max_chunks > (1ll << 30) || n_igroups * max_ichunks > (1ll << 30)) return false;

@@ -426,71 +426,6 @@ struct PingPongLds {
   float first[128];          // KS = 2: each row's offset after tile 0
 };
 
-// Query fragments of the lane's row (dims 16*ds + 8*hh + e): loaded raw, and,
-// once the tile DMAs are out, rotated and scaled by c.  quad: lanes of a quad
-// hold heads of one token (G a multiple of 4), so lane k of the quad
-// evaluates the angles of pairs k and k + 4 and the quad exchanges the rest.
-template <int D>
-struct PpQuery {
-  using M = Mfma<uint16_t>;
-  static constexpr int DP = D / 32;               // fragment ds pairs with ds + DP
-  bf16x8_t raw[2 * DP];
-  double theta[DP][2];
-  __device__ __forceinline__ void load_theta(const double* inv_freq, int lane) {
-#pragma unroll
-    for (int ds = 0; ds < DP; ++ds)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) theta[ds][u] = inv_freq[16 * ds + 8 * (lane >> 5) + 4 * u + (lane & 3)];
-  }
-  __device__ __forceinline__ void load(const uint16_t* src, int lane) {
-#pragma unroll
-    for (int ds = 0; ds < 2 * DP; ++ds) raw[ds] = M::load(src + 16 * ds + 8 * (lane >> 5));
-  }
-  __device__ __forceinline__ void rotate(bf16x8_t (&qf)[D / 16], const double* inv_freq, int64_t pos, float c,
-                                         bool quad, int lane) {
-#pragma unroll
-    for (int ds = 0; ds < DP; ++ds) {
-      float cs[8], sn[8];
-      if (quad) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          float ca, sa;
-          rope_cos_sin(pos, theta[ds][u], ca, sa);
-          ca *= c;
-          sa *= c;
-          cs[4 * u] = quad_bcast<0>(ca); sn[4 * u] = quad_bcast<0>(sa);
-          cs[4 * u + 1] = quad_bcast<1>(ca); sn[4 * u + 1] = quad_bcast<1>(sa);
-          cs[4 * u + 2] = quad_bcast<2>(ca); sn[4 * u + 2] = quad_bcast<2>(sa);
-          cs[4 * u + 3] = quad_bcast<3>(ca); sn[4 * u + 3] = quad_bcast<3>(sa);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          rope_cos_sin(pos, inv_freq[16 * ds + 8 * (lane >> 5) + e], cs[e], sn[e]);
-          cs[e] *= c;
-          sn[e] *= c;
-        }
-      }
-      f32x8_t x = M::to_f32v(raw[ds]), y = M::to_f32v(raw[ds + DP]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float xr, yr;
-        rope_rotate(x[e], y[e], cs[e], sn[e], xr, yr);
-        x[e] = xr;
-        y[e] = yr;
-      }
-      qf[ds] = M::from_f32(x);
-      qf[ds + DP] = M::from_f32(y);
-    }
-  }
-};
-
-__device__ __forceinline__ void phase_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  __syncthreads();
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 // KS = 1: 256 rows; both groups work through the same 64-key tiles, group B
 // (waves 4-7) half a step behind.  KS = 2: 128 rows; group A takes the even
 // tiles and B the odd ones for the same rows, and their states are combined

@@ -1,4 +1,5 @@
-// bf16 prefill unit on gfx950: eight waves in two groups of four that take
+// bf16 attention unit of the prefill and of the decode step's wide context
+// units on gfx950: eight waves in two groups of four that take
 // turns on the matrix cores.
 //
 // Rows are columns of the products here: a wave owns 32 query rows and works
@@ -218,9 +219,12 @@ __device__ __forceinline__ void pp_mask(f32x16_t& s, int lim, int lane) {
 // Softmax of one 64-key tile.  The offset is raised only when a score lies
 // more than kRescaleLog2 above it (then the sums and outputs are rescaled):
 // weights below 2^kRescaleLog2 are harmless in fp32.  A row that has seen no
-// key takes its first visible tile's max.
-template <int D>
-__device__ __forceinline__ void pp_softmax(f32x16_t (&s)[2], PpState<D>& st, bf16x8_t (&pf)[4]) {
+// key takes its first visible tile's max.  RAW: the queries do not carry the
+// softmax scale, so scores and offsets are raw and an exponent is c times
+// them (a query that is already rounded to bf16 would be rounded again by
+// scaling it).
+template <int D, bool RAW = false>
+__device__ __forceinline__ void pp_softmax(f32x16_t (&s)[2], PpState<D>& st, bf16x8_t (&pf)[4], float c = 1.f) {
   float mx = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
   for (int i = 1; i < 16; ++i) mx = fmaxf(fmaxf(mx, s[0][i]), s[1][i]);
@@ -228,8 +232,8 @@ __device__ __forceinline__ void pp_softmax(f32x16_t (&s)[2], PpState<D>& st, bf1
     const float m2 = xor32_max(mx);
     const bool fresh = st.thr == -INFINITY;
     const float d = fresh ? (m2 == -INFINITY ? 0.f : m2) : fmaxf(m2, 0.f);
-    const float alpha = fresh ? 0.f : fast_exp2(-d);
-    if (m2 > -INFINITY) st.thr = kRescaleLog2;
+    const float alpha = fresh ? 0.f : fast_exp2(RAW ? -d * c : -d);
+    if (m2 > -INFINITY) st.thr = RAW ? kRescaleLog2 / c : kRescaleLog2;
 #pragma unroll
     for (int k = 0; k < 4; ++k) st.l[k] *= alpha;
 #pragma unroll
@@ -248,13 +252,78 @@ __device__ __forceinline__ void pp_softmax(f32x16_t (&s)[2], PpState<D>& st, bf1
   for (int k = 0; k < 4; ++k) {
     f32x8_t p;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = fast_exp2(s[k >> 1][8 * (k & 1) + i]);
+    for (int i = 0; i < 8; ++i) p[i] = fast_exp2(RAW ? s[k >> 1][8 * (k & 1) + i] * c : s[k >> 1][8 * (k & 1) + i]);
     pf[k] = __builtin_convertvector(p, bf16x8_t);
     // the row sum adds the rounded weights, the ones the values are multiplied by
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       st.l[i] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2_t{pf[k][2 * i], pf[k][2 * i + 1]}, one, st.l[i], false);
   }
+}
+
+// Query fragments of the lane's row (dims 16*ds + 8*hh + e): loaded raw, and,
+// once the tile DMAs are out, rotated and scaled by c.  quad: lanes of a quad
+// hold heads of one token (G a multiple of 4), so lane k of the quad
+// evaluates the angles of pairs k and k + 4 and the quad exchanges the rest.
+template <int D>
+struct PpQuery {
+  using M = Mfma<uint16_t>;
+  static constexpr int DP = D / 32;               // fragment ds pairs with ds + DP
+  bf16x8_t raw[2 * DP];
+  double theta[DP][2];
+  __device__ __forceinline__ void load_theta(const double* inv_freq, int lane) {
+#pragma unroll
+    for (int ds = 0; ds < DP; ++ds)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) theta[ds][u] = inv_freq[16 * ds + 8 * (lane >> 5) + 4 * u + (lane & 3)];
+  }
+  __device__ __forceinline__ void load(const uint16_t* src, int lane) {
+#pragma unroll
+    for (int ds = 0; ds < 2 * DP; ++ds) raw[ds] = M::load(src + 16 * ds + 8 * (lane >> 5));
+  }
+  __device__ __forceinline__ void rotate(bf16x8_t (&qf)[D / 16], const double* inv_freq, int64_t pos, float c,
+                                         bool quad, int lane) {
+#pragma unroll
+    for (int ds = 0; ds < DP; ++ds) {
+      float cs[8], sn[8];
+      if (quad) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float ca, sa;
+          rope_cos_sin(pos, theta[ds][u], ca, sa);
+          ca *= c;
+          sa *= c;
+          cs[4 * u] = quad_bcast<0>(ca); sn[4 * u] = quad_bcast<0>(sa);
+          cs[4 * u + 1] = quad_bcast<1>(ca); sn[4 * u + 1] = quad_bcast<1>(sa);
+          cs[4 * u + 2] = quad_bcast<2>(ca); sn[4 * u + 2] = quad_bcast<2>(sa);
+          cs[4 * u + 3] = quad_bcast<3>(ca); sn[4 * u + 3] = quad_bcast<3>(sa);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          rope_cos_sin(pos, inv_freq[16 * ds + 8 * (lane >> 5) + e], cs[e], sn[e]);
+          cs[e] *= c;
+          sn[e] *= c;
+        }
+      }
+      f32x8_t x = M::to_f32v(raw[ds]), y = M::to_f32v(raw[ds + DP]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float xr, yr;
+        rope_rotate(x[e], y[e], cs[e], sn[e], xr, yr);
+        x[e] = xr;
+        y[e] = yr;
+      }
+      qf[ds] = M::from_f32(x);
+      qf[ds + DP] = M::from_f32(y);
+    }
+  }
+};
+
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 }  // namespace ippd
