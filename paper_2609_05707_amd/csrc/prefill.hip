@@ -554,7 +554,7 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
   bf16x8_t pf[4];
   uint32_t kst = 0, vst = 0;                      // stages of K and V of the group's tile
   if constexpr (KS == 1) {
-    wait_vmcnt<6 * PER>();
+    wait_tiles<2 * PER, 3>(min(nt, 4) - 1);
   } else {
     // tiles this wave fetches in its first product phase: V(grp + 2), K(grp + 3)
     if (grp == 0) {
@@ -592,7 +592,7 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
   for (int i = 0; i < steps; ++i) {
     const int t = KS * i + (KS == 2 ? grp : 0);   // the group's tile
     __builtin_amdgcn_s_setprio(0);
-    wait_vmcnt<4 * PER / KS>();
+    wait_tiles<2 * PER / KS, 2>(max(min(nt - 2 - t, 2), 0));   // the younger fetches with lanes
     phase_barrier();
     unsigned char* vt = sh.ring + R::VBASE + vst;
     if (tc.rem > 64 * KS && tc.at + 64 <= common) {
