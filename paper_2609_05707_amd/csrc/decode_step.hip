@@ -364,9 +364,8 @@ struct UnitLds {
   static constexpr int TASK = QAREA + (D / 2) * 8;                     // + (cos, sin) of its position
   static constexpr int MAIN = RING;
   // the segment units' small arrays, at the end of main
-  static constexpr int KV_BYTES = NW * D * static_cast<int>(sizeof(T));
-  static constexpr int EXTRA = 2 * KV_BYTES + NW * 16 * 8 + NW * 16 * 4 + NW * 4;
-  static constexpr int SEGMAIN = (MAIN - EXTRA) & ~15;
+  static constexpr int KV_BYTES = segment_kv_bytes(sizeof(T), D, NW);
+  static constexpr int SEGMAIN = segment_main_bytes(sizeof(T), D, NW, MAIN);
   static_assert(NW * TASK <= SEGMAIN, "segment tasks must fit");
   alignas(16) unsigned char main[MAIN];
   // per task: the segment's last key (the step's token) and its value
@@ -1078,9 +1077,9 @@ __device__ __forceinline__ void segment_unit(const StepParams& p, UnitLds<T, D, 
   const int ntiles = live ? (mem + 31) >> 5 : 0;
   const int mlast = max(mem - 1, 0);
   // sw waves of the task hold states to combine (all tasks' states must fit
-  // main); tile t goes to wave (t + 1) % sw, so the leader, busy with the
-  // queries first, takes tiles last
-  const int sw = min(wpt, L::SEGMAIN / (G * (D + 4) * 4) / tpu);
+  // main: the planner's tpu leaves at least one each); tile t goes to wave
+  // (t + 1) % sw, so the leader, busy with the queries first, takes tiles last
+  const int sw = min(wpt, L::SEGMAIN / (G * segment_state_row(D)) / tpu);
   const int first = ww < sw ? (ww + sw - 1) % sw : ntiles;
   unsigned char* qrows = sh.main + k * L::TASK;
   const unsigned char* qrow = qrows + lr * L::QROW + lg * 8 * E;
@@ -1397,18 +1396,9 @@ static hipError_t launch_attend(int grid, const StepParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Ring depth: 4 stages (two workgroups per CU) in general; 8 (one per CU,
-// every tile of a short unit in flight at once) when the context units fit
-// the chip in one wave, or when registers allow one workgroup per CU anyway.
-// fp32 at D = 128 has 32 KB stages: 2 or 4.  bf16 at D = 128 (16 KB stages)
-// takes the deepest rings the 160 KB of LDS allow: five stages (80 KB, two
-// workgroups per compute unit) or nine (one workgroup), so that each compute
-// unit keeps six or seven tiles in flight while it computes.
 template <typename T, int D, int NW, int RB>
 static hipError_t launch_depth(bool deep, int grid, const StepParams& p, hipStream_t s) {
-  constexpr int stage = 2 * 32 * D * sizeof(T);
-  constexpr int base = stage > 16384 ? 2 : (stage == 16384 ? 5 : 4);
-  constexpr int dns = stage > 16384 ? 4 : (stage == 16384 ? 9 : 8);
+  constexpr int base = ring_stages(sizeof(T), D, false), dns = ring_stages(sizeof(T), D, true);
   return deep ? launch_attend<T, D, NW, dns, RB>(grid, p, s) : launch_attend<T, D, NW, base, RB>(grid, p, s);
 }
 

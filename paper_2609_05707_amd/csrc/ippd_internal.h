@@ -17,6 +17,30 @@ constexpr int kDenseSegTiles = 8;              // dense-mask baseline: 32-token 
 constexpr int kMergeThreads = IPPD_MERGE_THREADS;   // merge_kernel workgroup size (256 measured ahead of 512
                                                     // when a call has few questions, equal otherwise)
 
+// LDS of the decode kernels, for element size e and head dimension D.  A ring
+// stage holds 32 keys and their values.  Ring depth: 4 stages (two workgroups
+// per CU) in general; 8 (one per CU, every tile of a short unit in flight at
+// once) when the context units fit the chip in one wave, or when registers
+// allow one workgroup per CU anyway.  fp32 at D = 128 has 32 KB stages: 2 or
+// 4.  bf16 at D = 128 (16 KB stages) takes the deepest rings the 160 KB of LDS
+// allow: five stages (80 KB, two workgroups per compute unit) or nine (one
+// workgroup), so that each compute unit keeps six or seven tiles in flight
+// while it computes.
+constexpr int ring_stage_bytes(int e, int D) { return 2 * 32 * D * e; }
+constexpr int ring_stages(int e, int D, bool deep) {
+  const int stage = ring_stage_bytes(e, D);
+  return stage > 16384 ? (deep ? 4 : 2) : stage == 16384 ? (deep ? 9 : 5) : (deep ? 8 : 4);
+}
+// A segment unit's part of the ring: the small arrays of its `waves` tasks
+// (last key and value, per-wave (max, sum), last scores, served marks) sit at
+// the end, and the rest holds the tasks' query rows and later the partial
+// state of each serving wave, G rows of segment_state_row bytes.
+constexpr int segment_kv_bytes(int e, int D, int waves) { return waves * D * e; }
+constexpr int segment_main_bytes(int e, int D, int waves, int ring_bytes) {
+  return (ring_bytes - (2 * segment_kv_bytes(e, D, waves) + waves * 16 * 8 + waves * 16 * 4 + waves * 4)) & ~15;
+}
+constexpr int segment_state_row(int D) { return (D + 4) * 4; }
+
 struct LoadContextParams {
   const void* k_raw; const void* v_raw;     // [pool][Hkv][D]
   void* ctx_k; void* ctx_vt;

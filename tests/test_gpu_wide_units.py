@@ -128,3 +128,24 @@ def test_segments_after_the_context_units(hkv, g, instr, mode):
         assert (got[t][~si.active] == -555.0).all()
     np.testing.assert_array_equal(db.seg_len[0][: st.num_questions].cpu().numpy(), st.seg_len_at(2))
     assert db.err_flag() == 0
+
+
+@pytest.mark.parametrize("g", [14, 15])
+def test_segment_tasks_of_wide_groups(g):
+    """Head dim 64, 14 and 15 heads per kv head, more segment tasks than the
+    chip holds beside the context units: a task keeps a wave's state in the
+    unit's LDS however many tasks share the unit, and its cached keys count."""
+    log(f"case: segment tasks D=64 G={g}")
+    wl = W.custom_workload(wid=790 + g, dtype="bf16", num_prompts=6, hq=g, hkv=1, head_dim=64, ctx_len=(88, 96),
+                           questions=(256, 256), seg_len=(2, 40), steps=1, value_std=0.5)
+    st = W.make_structure(wl)
+    kv = W.layer_kv(st)
+    db = make_batch(st)
+    poison(db)
+    load_layer(db, st, 0, kv)
+    gpu = run_gpu(st, [0], [0], db=db, kv=kv, fused=True)
+    ask = list(range(0, st.num_questions, 23))
+    out, lse = oracle_steps(st, kv, [0], [0], questions={0: ask})[0]
+    e = max_err(gpu.out[0][ask], out[ask]), max_err(gpu.lse[0][ask], lse[ask])
+    log(f"  {len(ask)} questions, max err {e[0]:.3e}, lse {e[1]:.3e}")
+    assert gpu.err == 0 and e[0] <= TOL and e[1] <= TOL
