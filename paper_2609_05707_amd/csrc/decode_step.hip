@@ -891,12 +891,12 @@ __device__ __forceinline__ void context_unit_pp(const StepParams& p, unsigned ch
     wait_step(t);
     phase_barrier();
     const unsigned char* vt = ring + R::VBASE + vst;
-    const int rem = ntok - 64 * min(t, last);
-    if (rem < 64 || t > last) {
-      const int n0 = min(rem, 32), n1 = rem > 32 ? min(rem - 32, 32) : n0;
-      pp_mask(s[0], t > last ? -1 : n0 - 1, lane);
-      pp_mask(s[1], t > last || rem <= 32 ? -1 : n1 - 1, lane);
-      pp_clear_tail<D>(ring + R::VBASE + vst, n0, lane);
+    const int rem = t > last ? 0 : ntok - 64 * t;
+    if (rem < 64) {                                // tokens of either half (0: it repeats another)
+      const int n0 = min(rem, 32), n1 = max(rem - 32, 0);
+      pp_mask(s[0], n0 - 1, lane);
+      pp_mask(s[1], n1 - 1, lane);
+      if (n0 < 32) pp_clear_tail<D>(ring + R::VBASE + vst, n0, lane);
       pp_clear_tail<D>(ring + R::VBASE + vst + R::HALF, n1, lane);
     }
     pp_softmax<D, true>(s, st, pf, c);

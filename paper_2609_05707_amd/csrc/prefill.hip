@@ -602,9 +602,9 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
 #pragma unroll
       for (int hf = 0; hf < 2 * KS; ++hf) {
         if (hf < 2) {
-          // tokens the half holds, and those of them the row sees
-          const int n = min(32, tc.rem);
-          const int l = 2 * t + hf < nh ? min(vis - tc.at, n - 1) : -1;
+          // tokens the half holds (0: it repeats the last), and those of them the row sees
+          const int n = 2 * t + hf < nh ? min(32, tc.rem) : 0;
+          const int l = min(vis - tc.at, n - 1);
           if (wave_any(l < 31)) pp_mask(s[hf], l, lane);
           if (n < 32) pp_clear_tail<D>(vt + hf * R::HALF, n, lane);
         }

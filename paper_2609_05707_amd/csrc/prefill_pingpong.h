@@ -99,13 +99,12 @@ struct PpFetch {
   }
 };
 
-// Zeroes the values past token n of a half tile whose last block is partial,
-// in that block and in the copies of it that follow: they may hold anything,
-// and a weight of 0 times NaN is NaN.  Each wave that will read them does it
-// (all write the same zeros).
+// Zeroes the values of a half tile past its n < 32 tokens (n = 0: a half that
+// only repeats another): in the last block they may hold anything, the blocks
+// after it are copies of that block, and a weight of 0 times NaN or infinity
+// is NaN.  Each wave that will read them does it (all write the same zeros).
 template <int D>
 __device__ __forceinline__ void pp_clear_tail(unsigned char* vhalf, int n, int lane) {
-  if ((n & 7) == 0) return;
   for (int b = n >> 3; b < 4; ++b)
 #pragma unroll
     for (int d = 0; d < D; d += 64) {
