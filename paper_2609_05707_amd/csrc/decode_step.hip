@@ -413,7 +413,7 @@ struct CtxUnit {
 // Locates the workgroup's unit of RW rows; false if it has nothing to stream.
 // The lane's rows are row0 + first + 16 * rb, and lanes below `lead` hold each
 // of the wave's rows once.
-template <bool FUSED, int RW, int RB, bool INSTR>
+template <bool FUSED, int RW, int RB, bool INSTR, int TILE>
 __device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<RB>& cu, int first, int lead, int lane) {
   // instruction units follow the context units (blockIdx >= ctx_blocks)
   const unsigned ub = INSTR ? blockIdx.x - static_cast<unsigned>(p.ctx_blocks) : blockIdx.x;
@@ -490,12 +490,13 @@ __device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<R
     if (FUSED && p.S > 0) pos_base = instr_pos_base(p.instr_start, p.instr_len, p.S, b);
   }
   // the prompt's context is split into n = ceil(len / chunk) equal chunks
-  // (whole tiles), so that a short last chunk does not leave its unit idle;
-  // instruction chunks keep the planned size
+  // of whole tiles (TILE keys: a chunk that ends inside one costs as much), so
+  // that a short last chunk does not leave its unit idle; instruction chunks
+  // keep the planned size
   int cb = p.chunk;
   if (!INSTR && ctx_len > 0) {
     const int n = (ctx_len + p.chunk - 1) / p.chunk;
-    cb = (((ctx_len + n - 1) / n) + 31) & ~31;
+    cb = (((ctx_len + n - 1) / n) + TILE - 1) & ~(TILE - 1);
   }
   const int G = p.G;
   const int row0 = rg * RW;
@@ -563,7 +564,7 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   constexpr int P0 = RG::NS - 1 < 3 ? RG::NS - 1 : 3;      // tiles issued before the queries are rotated
   const int lr = lane & 15, lg = lane >> 4;
   CtxUnit<RB> cu;
-  if (!find_context_unit<FUSED, RW, RB, INSTR>(p, cu, 16 * RB * wave + lr, 16, lane)) return;
+  if (!find_context_unit<FUSED, RW, RB, INSTR, 32>(p, cu, 16 * RB * wave + lr, 16, lane)) return;
   const int G = p.G, g = cu.g;
   const int64_t k0 = cu.k0, k1 = cu.k1;
   const int ntiles = static_cast<int>((k1 - k0 + 31) >> 5);
@@ -739,7 +740,7 @@ __device__ __forceinline__ void context_unit_pp(const StepParams& p, unsigned ch
   if (FUSED && quad) query.load_theta(p.inv_freq, lane);   // shares the lookups' round trips
   const int grp = wave >> 2, rw = KS == 1 ? wave : wave & 3;
   CtxUnit<1> cu;
-  if (!find_context_unit<FUSED, 256 / KS, 1, INSTR>(p, cu, 32 * rw + (lane & 31), 32, lane)) return;
+  if (!find_context_unit<FUSED, 256 / KS, 1, INSTR, 64>(p, cu, 32 * rw + (lane & 31), 32, lane)) return;
   const int row = cu.row0 + 32 * rw + (lane & 31);
   const bool in_range = row < cu.nrows;
   const int qi = in_range ? cu.qsel[0] : cu.qa;    // (rows past the active ones are never published)
