@@ -419,6 +419,9 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 1) void prefill_kernel(Prefi
 // ---------------------------------------------------------------------------
 // bf16: 32 rows per wave, two wave groups half a step apart (prefill_pingpong.h).
 // ---------------------------------------------------------------------------
+// Values of a half tile past a unit's last key.
+static __device__ __align__(16) uint16_t zero_half[32 * 128];
+
 template <int D>
 struct PingPongLds {
   alignas(16) unsigned char ring[PpRing<D>::BYTES];
@@ -468,8 +471,8 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
   KeyCursor ti, tc;
   ti.region(ks, 0);
   tc = ti;
-  // the halves of a tile to be fetched; halves past the last repeat it
-  // (finite data, masked)
+  // the halves of a tile to be fetched; halves past the last repeat its keys
+  // (masked) and take zeros for values: a weight of 0 times an infinity is NaN
   struct Half {
     const T *k, *v;
     int n;
@@ -497,6 +500,7 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
         const int64_t so = ((static_cast<int64_t>(un.qa + ks.jlo + ti.reg - 2) * p.Hkv + un.g) * p.seg_cap + ti.at) * D;
         ht[hf] = Half{static_cast<const T*>(p.seg_k) + so, static_cast<const T*>(p.seg_vt) + so, min(32, ti.rem)};
       }
+      if (hin >= nh) ht[hf].v = zero_half;
       if (++hin < nh) ti.next(ks);
     }
   };
@@ -606,7 +610,7 @@ __device__ __forceinline__ void pingpong_unit(const PrefillParams& p, PingPongLd
           const int n = 2 * t + hf < nh ? min(32, tc.rem) : 0;
           const int l = min(vis - tc.at, n - 1);
           if (wave_any(l < 31)) pp_mask(s[hf], l, lane);
-          if (n < 32) pp_clear_tail<D>(vt + hf * R::HALF, n, lane);
+          if (n > 0 && n < 32) pp_clear_tail<D>(vt + hf * R::HALF, n, lane);
         }
         if (2 * t + hf + 1 < nh && tc.next(ks)) {
           vis = region_limit(un, ks, row, tc.reg);

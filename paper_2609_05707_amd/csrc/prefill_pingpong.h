@@ -102,11 +102,21 @@ struct PpFetch {
 // Zeroes the values of a half tile past its n < 32 tokens (n = 0: a half that
 // only repeats another): in the last block they may hold anything, the blocks
 // after it are copies of that block, and a weight of 0 times NaN or infinity
-// is NaN.  Each wave that will read them does it (all write the same zeros).
+// is NaN.  Each wave that will read them does it (all write the same zeros);
+// if the last block is finite, and so are its copies, nothing has to be done.
+// (Writing always cost a prefill of 3 questions of 8 tokens 1 of 33 us.)
 template <int D>
 __device__ __forceinline__ void pp_clear_tail(unsigned char* vhalf, int n, int lane) {
-  // (only the last block is read: with each block read, masked and written back
-  // the last tile cost a 59 us step 0.8 us)
+  if (n > 0) {
+    bool any = false;
+#pragma unroll
+    for (int d = 0; d < D; d += 64) {
+      const u16x8_t x = *reinterpret_cast<const u16x8_t*>(vhalf + ((n - 1) >> 3) * (16 * D) + (d + lane) * 16);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) any = any || (x[k] & 0x7F80) == 0x7F80;
+    }
+    if (!wave_any(any)) return;
+  }
 #pragma unroll 1
   for (int b = n >> 3; b < 4; ++b) {
 #pragma unroll
