@@ -1397,30 +1397,30 @@ static hipError_t launch_attend(int grid, const StepParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int D, int NW, int RB>
-static hipError_t launch_depth(bool deep, int grid, const StepParams& p, hipStream_t s) {
-  constexpr int base = ring_stages(sizeof(T), D, false), dns = ring_stages(sizeof(T), D, true);
-  return deep ? launch_attend<T, D, NW, dns, RB>(grid, p, s) : launch_attend<T, D, NW, base, RB>(grid, p, s);
+// Only fp32 units have both rings (see unit_kind in plan.h).
+template <typename T, int D, int NW>
+static hipError_t launch_ring(bool deep, int grid, const StepParams& p, hipStream_t s) {
+  if constexpr (sizeof(T) == 4)
+    if (deep) return launch_attend<T, D, NW, ring_stages(sizeof(T), D, true), 1>(grid, p, s);
+  return launch_attend<T, D, NW, ring_stages(sizeof(T), D, false), 1>(grid, p, s);
 }
 
 template <typename T, int D>
 static hipError_t launch_waves(int waves, int rb, bool deep, int grid, const StepParams& p, hipStream_t s) {
-  if (rb == 2) {
-    if constexpr (sizeof(T) == 2 && D == 128) {
-      if (waves == 8) return launch_attend<T, D, 8, 9, 2>(grid, p, s);
-    }
-    return hipErrorInvalidValue;
+  // bf16 at D = 128 with eight waves is the two-group unit
+  if constexpr (sizeof(T) == 2 && D == 128) {
+    constexpr int kStages = ring_stages(sizeof(T), D, true);
+    if (waves == 8) return rb == 2 ? launch_attend<T, D, 8, kStages, 2>(grid, p, s) : launch_attend<T, D, 8, kStages, 1>(grid, p, s);
   }
+  if (rb != 1) return hipErrorInvalidValue;
   switch (waves) {
-    case 1: return launch_depth<T, D, 1, 1>(deep, grid, p, s);
-    case 2: return launch_depth<T, D, 2, 1>(deep, grid, p, s);
-    case 4: return launch_depth<T, D, 4, 1>(deep, grid, p, s);
+    case 1: return launch_ring<T, D, 1>(deep, grid, p, s);
+    case 2: return launch_ring<T, D, 2>(deep, grid, p, s);
+    case 4: return launch_ring<T, D, 4>(deep, grid, p, s);
     default:
-      // the planner gives fp32 at D = 128 at most four waves; bf16 at D = 128
-      // with eight is the two-group unit, one workgroup per compute unit
-      if constexpr (D == 128 && sizeof(T) == 4) return hipErrorInvalidValue;
-      else if constexpr (D == 128) return launch_attend<T, D, 8, 9, 1>(grid, p, s);
-      else return launch_depth<T, D, 8, 1>(deep, grid, p, s);
+      // (the planner gives fp32 at D = 128 at most four waves)
+      if constexpr (D == 128) return hipErrorInvalidValue;
+      else return launch_ring<T, D, 8>(deep, grid, p, s);
   }
 }
 

@@ -18,14 +18,11 @@ constexpr int kMergeThreads = IPPD_MERGE_THREADS;   // merge_kernel workgroup si
                                                     // when a call has few questions, equal otherwise)
 
 // LDS of the decode kernels, for element size e and head dimension D.  A ring
-// stage holds 32 keys and their values.  Ring depth: 4 stages (two workgroups
-// per CU) in general; 8 (one per CU, every tile of a short unit in flight at
-// once) when the context units fit the chip in one wave, or when registers
-// allow one workgroup per CU anyway.  fp32 at D = 128 has 32 KB stages: 2 or
-// 4.  bf16 at D = 128 (16 KB stages) takes the deepest rings the 160 KB of LDS
-// allow: five stages (80 KB, two workgroups per compute unit) or nine (one
-// workgroup), so that each compute unit keeps six or seven tiles in flight
-// while it computes.
+// stage holds 32 keys and their values.  Depth, for two workgroups per compute
+// unit or (deep) for one: 4 or 8 stages of up to 16 KB in general; fp32 at D =
+// 128 has 32 KB stages, 2 or 4; bf16 at D = 128 (16 KB stages) takes the
+// deepest rings the 160 KB of LDS allow, 5 or 9, so that each compute unit
+// keeps six or seven tiles in flight while it computes.
 constexpr int ring_stage_bytes(int e, int D) { return 2 * 32 * D * e; }
 constexpr int ring_stages(int e, int D, bool deep) {
   const int stage = ring_stage_bytes(e, D);
@@ -86,7 +83,7 @@ struct StepPlan {
   int ctx_blocks;          // context units (8 * nrg * ceil(n_groups * max_chunks / 8))
   int seg_blocks;          // segment units: ceil(Nt * Hkv / seg_tpu)
   int seg_tpu;             // segment tasks per unit (power of two dividing waves)
-  int deep;                // 1: deep LDS ring (the context units fit the chip in one wave)
+  int deep;                // 1: fp32 units with the deep LDS ring, one workgroup per compute unit
   int n_igroups;           // instruction groups: (instruction s, kv head g) or (question i, kv head g)
   int nrg_i;               // row groups per instruction group
   int max_ichunks;         // ceil(max_instr_len / chunk)

@@ -23,7 +23,7 @@ def batch(**k):
 
 @pytest.mark.parametrize("dtype,heads,d,ctx,q,chunks", [
     (L.IPPD_DTYPE_F32, (4, 2), 64, 256, 4, 8),          # 32 tokens: eight units per kv head instead of one
-    (L.IPPD_DTYPE_BF16, (32, 8), 128, 512, 4, 16),      # 32 tokens
+    (L.IPPD_DTYPE_BF16, (32, 8), 128, 512, 4, 8),       # 64 tokens
     (L.IPPD_DTYPE_BF16, (32, 8), 128, 32768, 64, 24),   # 256-row units: segment units resident beside them
 ])
 def test_chunks(lib, dtype, heads, d, ctx, q, chunks):  # noqa: F811
