@@ -4,31 +4,27 @@ tile and the 128 keys of a step of the two-group unit; keys that keep growing
 (the softmax offset is raised again and again); cache memory past every
 region holding NaN.  Against the fp64 oracle.
 
-Tolerance: the rotated operands and the weights are rounded to bf16 (relative
-2^-9 each), so a score is off by at most ds = 2 * 2^-9 * scale * sum |q||k|,
-a weight by a factor within exp(+-ds)(1 +- 2^-9), numerator and denominator
-alike: |out - ref| <= max|v| * (2 ds + 2^-8), computed from the inputs."""
+Tolerances.  Against the oracle, which rounds nothing: the rotated operands and
+the weights are rounded to bf16 (relative 2^-9 each), so a score is off by at
+most ds = 2 * 2^-9 * scale * sum |q||k|, a weight by a factor within
+exp(+-ds)(1 +- 2^-9), numerator and denominator alike: |out - ref| <= max|v| *
+(2 ds + 2^-8), computed from the inputs.  That bound is wide, so the same is
+compared with fp64 over the rounded operands, where only the weights' rounding
+is left (rounded_reference.py): the queries are rounded there from fp64 and in
+the kernel from fp32, which a few in 2^15 elements straddle, so all but one in
+a thousand outputs have to lie within that bound.  test_prefill_edges_power.py
+shows on the CPU that hiding one key at the edge of a tile is seen."""
 import numpy as np
 import pytest
 import torch
 
-import workload as W
 from oracle import prefill as P
 from paper_2609_05707_amd.session import DecodeBatch
 from tests.gpu_harness import log, max_err
+from tests.prefill_edges import CASES, inputs, reference
+from tests.rounded_reference import beyond
 
 pytestmark = pytest.mark.gpu
-
-CASES = [
-    # (name, hq, hkv, D, context lengths, question lengths per prompt, growth of the keys per token)
-    ("one-key", 4, 1, 128, [1, 0, 31], [[1], [1, 32], [33]], 0.0),
-    ("tile-edges", 8, 2, 128, [32, 33, 63, 64, 65], [[31], [64], [65, 1], [], [5, 0, 7]], 0.0),
-    ("step-edges", 8, 1, 128, [127, 128, 129, 193, 260], [[3], [40, 40], [64], [1], [96, 33]], 0.0),
-    ("growing", 4, 1, 128, [300, 97], [[70, 5], [33]], 0.05),
-    ("g3", 6, 2, 128, [86, 170], [[85, 1], [43]], 0.0),
-    ("d64", 4, 1, 64, [1, 64, 65, 129, 200], [[1], [32, 33], [], [64], [127]], 0.0),
-    ("d64-growing-g16", 16, 1, 64, [150, 33], [[9, 17], [40]], 0.05),
-]
 
 
 @pytest.mark.parametrize("standard", [False, True])
@@ -39,19 +35,9 @@ def test_prefill_edges(case, rows, standard):
     if d == 64 and rows == 256:
         pytest.skip("256-row units are asked for at head_dim 128 only")
     log(f"case: prefill edges {name} tile_rows={rows} standard={standard}")
-    rng = np.random.default_rng([930, CASES.index(case)])
     qn = [n for p in ql for n in p]
     q_count = [len(p) for p in ql]
-    nc, ns = sum(lc), sum(qn)
-
-    def draw(n, h):
-        return W.round_to_bf16(rng.standard_normal((n, h, d)).astype(np.float32) * np.float32(0.5))
-
-    pos_c = np.concatenate([np.arange(n) for n in lc])
-    pos_s = np.concatenate([lc[b] + np.arange(n) for b, p in enumerate(ql) for n in p])
-    ck, cv, cq, sk, sv, sq = draw(nc, hkv), draw(nc, hkv), draw(nc, hq), draw(ns, hkv), draw(ns, hkv), draw(ns, hq)
-    ck = W.round_to_bf16(ck * (1 + grow * pos_c)[:, None, None].astype(np.float32))
-    sk = W.round_to_bf16(sk * (1 + grow * pos_s)[:, None, None].astype(np.float32))
+    ck, cv, cq, sk, sv, sq = inputs(case)
     db = DecodeBatch(lc, q_count, hq, hkv, d, "bf16", max(qn), tile_rows=rows)
     for x in (db.ctx_k[0], db.ctx_vt[0], db.seg_k[0], db.seg_vt[0]):
         x.fill_(float("nan"))
@@ -82,3 +68,16 @@ def test_prefill_edges(case, rows, standard):
     assert np.isfinite(g_ctx).all() and np.isfinite(g_seg).all()
     assert e_ctx <= tol and e_seg <= tol
     assert db.err_flag() == 0
+    # over the rounded keys of the cache
+    kc = db.ctx_k[0].float().cpu().numpy()
+    kc = np.concatenate([kc[:, db.ctx_off[b]: db.ctx_off[b] + lc[b]] for b in range(len(lc))], 1)
+    ks = db.seg_k[0].float().cpu().numpy()
+    ks = np.concatenate([ks[i, :, :n] for i, n in enumerate(qn)], 1)
+    (o_ctx, b_ctx), (o_seg, b_seg) = reference(case, kc, ks)
+    if standard:
+        served = np.concatenate([np.full(n, c > 0) for n, c in zip(lc, q_count)])
+        g_ctx, o_ctx, b_ctx = g_ctx[served], o_ctx[served], b_ctx[served]
+    for what, g, o, e in (("ctx", g_ctx, o_ctx, b_ctx), ("questions", g_seg, o_seg, b_seg)):
+        share, most = beyond(g, o, e)
+        log(f"  {what}: {share:.2e} of the outputs beyond the weights' rounding, largest {most:.2f} times it")
+        assert share <= 1e-3

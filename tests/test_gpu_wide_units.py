@@ -4,7 +4,11 @@ tiles: contexts of 1 to 5 tiles with empty, partial and whole halves, chunks
 that end inside a tile, 1 to 16 heads per kv head (quads that do and do not
 share a question), waves and a whole wave group without active rows, and
 instruction units.  The caches hold NaN where nothing is loaded.  Tolerance
-2e-2: operands and weights are rounded to 8 bits, as everywhere in bf16."""
+2e-2: operands and weights are rounded to 8 bits, as everywhere in bf16.  As
+that hides a lost key of a long context, the outputs and log sums are also
+compared with fp64 over the call's own rounded queries and cached keys, where
+only the weights' rounding is left (rounded_reference.py): one key of n moves a
+log sum by about 1 / n, the bound is 2^-9."""
 import numpy as np
 import pytest
 
@@ -12,6 +16,7 @@ import workload as W
 from oracle import ippd as O
 from paper_2609_05707_amd.session import DecodeBatch
 from tests.gpu_harness import load_layer, log, make_batch, max_err, oracle_steps, run_gpu
+from tests.rounded_reference import EPS, attend, beyond
 from tests.test_gpu_twolevel import run_steps
 
 pytestmark = pytest.mark.gpu
@@ -23,6 +28,30 @@ def poison(db):
     for bufs in (db.ctx_k, db.ctx_vt, db.seg_k, db.seg_vt):
         for x in bufs:
             x.fill_(float("nan"))
+
+
+def check_rounded(db, st, gpu, t):
+    """Step t's outputs against fp64 over its rotated queries, the cached keys and values."""
+    si = W.step_inputs(st, t)
+    kc, vc = db.ctx_k[0].double().cpu().numpy(), db.ctx_values(0).double().cpu().numpy()
+    ks, vs = db.seg_k[0].double().cpu().numpy(), db.seg_values(0).double().cpu().numpy()
+    n, g, d = st.seg_len_at(t + 1), db.hq // db.hkv, db.D
+    share, most, off = [], 0.0, 0.0
+    for b in range(len(st.ctx_len)):
+        c = slice(int(db.ctx_off[b]), int(db.ctx_off[b] + st.ctx_len[b]))
+        for i in range(st.q_start[b], st.q_start[b + 1]):
+            if not si.active[i]:
+                continue
+            for k in range(db.hkv):
+                key = np.concatenate([kc[k, c], ks[i, k, : n[i]]])
+                val = np.concatenate([vc[k, :, c].T, vs[i, k, :, : n[i]].T])
+                h = slice(k * g, k * g + g)
+                out, bound, lse = attend(gpu.q_rot[t][i, h].astype(np.float64) @ key.T / np.sqrt(d), val)
+                s, m = beyond(gpu.out[t][i, h], out, bound)
+                share.append(s)
+                most, off = max(most, m), max(off, float(np.abs(gpu.lse[t][i, h] - lse).max()))
+    log(f"  step {t}: {np.mean(share):.1e} of the outputs beyond the weights' rounding, largest {most:.2f} times it; lse {off:.1e}")
+    assert np.mean(share) == 0 and off <= EPS + 2e-5
 
 
 CASES = [
@@ -62,6 +91,7 @@ def test_wide_units(case, rows, fused):
         log(f"  step {t}: {int(act.sum())} active, max err {e[0]:.3e}, lse {e[1]:.3e}")
         assert np.isfinite(gpu.out[t]).all() and e[0] <= TOL and e[1] <= TOL
         assert (gpu.out[t][~act] == -555.0).all()
+        check_rounded(db, st, gpu, t)
 
 
 @pytest.mark.parametrize("mode", ["fused", "separate"])
