@@ -168,17 +168,15 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int k) {
 }
 
 // Active-set compaction of the question range [qa, qb): the number of
-// active questions, and for each of the lane's row blocks the kq[rb]-th of
-// them (-1 if there are fewer).  Questions that have stopped (Sec. 4.2: a
+// active questions, and the kq-th of them for the lane's row (-1 if there are
+// fewer).  Questions that have stopped (Sec. 4.2: a
 // finished answer takes no further tokens) then hold no rows, so a unit's
 // rows are the G heads of its prompt's active questions in order.  Whole
 // wave: 64 flags per ballot, four windows per round of loads.
-template <int RB>
-__device__ __forceinline__ int active_questions(const uint8_t* __restrict__ active, int qa, int qb,
-                                                const int (&kq)[RB], int (&qsel)[RB], int lane) {
+__device__ __forceinline__ int active_questions(const uint8_t* __restrict__ active, int qa, int qb, int kq, int& qsel,
+                                                int lane) {
   int n = 0;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) qsel[rb] = -1;
+  qsel = -1;
   for (int w0 = qa; w0 < qb; w0 += 256) {
     // every load unconditional (lanes past qb read flag qb - 1), so that the
     // four go out together
@@ -192,11 +190,8 @@ __device__ __forceinline__ int active_questions(const uint8_t* __restrict__ acti
     for (int u = 0; u < 4; ++u) {
       const uint64_t m = __ballot(f[u]);
       const int c = __popcll(m);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int k = kq[rb] - n;
-        if (k >= 0 && k < c) qsel[rb] = w0 + 64 * u + nth_set_bit(m, k);
-      }
+      const int k = kq - n;
+      if (k >= 0 && k < c) qsel = w0 + 64 * u + nth_set_bit(m, k);
       n += c;
     }
   }
@@ -219,33 +214,28 @@ __device__ __forceinline__ u32x4_t gload_b128(const void* p) {
   return r;
 }
 
-template <typename T, int D, bool FUSED, int RB>
+template <typename T, int D, bool FUSED>
 struct RowLoads {
   static constexpr int QN = D * static_cast<int>(sizeof(T)) / 64;   // 16-byte query pieces per lane and row
   static constexpr int QPF = static_cast<int>(sizeof(T)) / 2;       // pieces per 8-element fragment
   static constexpr int TN = FUSED ? D / 16 : 0;                    // 16-byte pieces of the lane's D/8 frequencies
-  uint32_t a[RB], s[RB];
-  u32x4_t q[RB][QN];
+  uint32_t a, s;
+  u32x4_t q[QN];
   u32x4_t th[TN > 0 ? TN : 1];
 };
 
-// Lane (lg, lr) of row block rb (question qi[rb], head h[rb]): dims
-// 32*ds + 8*lg + u of the query (raw q_new in the fused step, rotated
-// q_rot_in otherwise).
-template <typename T, int D, bool FUSED, int RB>
-__device__ __forceinline__ void issue_row_loads(RowLoads<T, D, FUSED, RB>& r, const StepParams& p, const int (&qi)[RB],
-                                                const int (&h)[RB], int lg) {
-  using RL = RowLoads<T, D, FUSED, RB>;
+// Lane (lg, lr) of a row (question qi, head h): dims 32*ds + 8*lg + u of the
+// query (raw q_new in the fused step, rotated q_rot_in otherwise).
+template <typename T, int D, bool FUSED>
+__device__ __forceinline__ void issue_row_loads(RowLoads<T, D, FUSED>& r, const StepParams& p, int qi, int h, int lg) {
+  using RL = RowLoads<T, D, FUSED>;
+  r.a = gload_u8(p.active + qi);
+  r.s = gload_b32(p.seg_len + qi);
+  const char* src = static_cast<const char*>(FUSED ? p.q_new : p.q_rot_in) +
+                    ((static_cast<int64_t>(qi) * p.Hq + h) * D + lg * 8) * static_cast<int64_t>(sizeof(T));
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    r.a[rb] = gload_u8(p.active + qi[rb]);
-    r.s[rb] = gload_b32(p.seg_len + qi[rb]);
-    const char* src = static_cast<const char*>(FUSED ? p.q_new : p.q_rot_in) +
-                      ((static_cast<int64_t>(qi[rb]) * p.Hq + h[rb]) * D + lg * 8) * static_cast<int64_t>(sizeof(T));
-#pragma unroll
-    for (int k = 0; k < RL::QN; ++k)
-      r.q[rb][k] = gload_b128(src + (k / RL::QPF) * 32 * static_cast<int>(sizeof(T)) + (k % RL::QPF) * 16);
-  }
+  for (int k = 0; k < RL::QN; ++k)
+    r.q[k] = gload_b128(src + (k / RL::QPF) * 32 * static_cast<int>(sizeof(T)) + (k % RL::QPF) * 16);
   if constexpr (FUSED) {
     // theta of pairs 32*ds + 8*lg + u, u = 0..7: 64 contiguous bytes per ds,
     // read where the launch placed StepParams (the kernel's only argument)
@@ -259,17 +249,13 @@ __device__ __forceinline__ void issue_row_loads(RowLoads<T, D, FUSED, RB>& r, co
 // The one wait for the row loads: s_waitcnt vmcnt(N), then every destination
 // register is tied to an asm statement at that point, so that none is read
 // (or copied) before it (volatile asm statements keep their order).
-template <int N, typename T, int D, bool FUSED, int RB>
-__device__ __forceinline__ void wait_row_loads(RowLoads<T, D, FUSED, RB>& r) {
+template <int N, typename T, int D, bool FUSED>
+__device__ __forceinline__ void wait_row_loads(RowLoads<T, D, FUSED>& r) {
   static_assert(N >= 0 && N < 64, "vmcnt range");
-  using RL = RowLoads<T, D, FUSED, RB>;
-  asm volatile("s_waitcnt vmcnt(%2)" : "+v"(r.a[0]), "+v"(r.s[0]) : "n"(N));
+  using RL = RowLoads<T, D, FUSED>;
+  asm volatile("s_waitcnt vmcnt(%2)" : "+v"(r.a), "+v"(r.s) : "n"(N));
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    if (rb > 0) asm volatile("" : "+v"(r.a[rb]), "+v"(r.s[rb]));
-#pragma unroll
-    for (int k = 0; k < RL::QN; ++k) asm volatile("" : "+v"(r.q[rb][k]));
-  }
+  for (int k = 0; k < RL::QN; ++k) asm volatile("" : "+v"(r.q[k]));
 #pragma unroll
   for (int k = 0; k < RL::TN; ++k) asm volatile("" : "+v"(r.th[k]));
 }
@@ -282,7 +268,7 @@ __device__ __forceinline__ double lane_theta(const u32x4_t (&th)[TN], int ds, in
   return __hiloint2double(static_cast<int>(tp[2 * (u & 1) + 1]), static_cast<int>(tp[2 * (u & 1)]));
 }
 
-// Query fragments (B operand) of one row block from its loaded pieces,
+// Query fragments (B operand) of the rows from their loaded pieces,
 // rotated at pos in the fused step.  Pair j < D/2 is (x_j, x_{j+D/2}):
 // fragments ds and ds + DS/2.  quad: the four lanes of each lane quad hold
 // heads of one question (G a multiple of 4), so they share every angle:
@@ -386,11 +372,10 @@ struct UnitLds {
 };
 
 // ---------------------------------------------------------------------------
-// Context unit.  blockIdx -> slice (XCD) = blockIdx & 7, local = blockIdx >> 3;
-// consecutive locals of a slice are the row groups of one chunk (they share
-// its tiles through that XCD's L2) and chunks are dealt to the slices round
-// robin.
-// ---------------------------------------------------------------------------
+// Context units (context_unit, context_unit_pp).  blockIdx -> slice (XCD) =
+// blockIdx & 7, local = blockIdx >> 3; consecutive locals of a slice are the
+// row groups of one chunk (they share its tiles through that XCD's L2) and
+// chunks are dealt to the slices round robin.
 //
 // INSTR: an instruction unit of a two-level batch: the group is
 // (instruction s, kv head g), whose rows are the questions of every prompt
@@ -398,23 +383,23 @@ struct UnitLds {
 // instruction's chunk, and the states go to the instruction slots
 // max_chunks + 1 + chunk.  In the fused step each row's query is rotated at
 // its own question's position instr_len[s] + ctx_len[b] + seg_len[i].
-// The unit a workgroup serves: its group's keys and the questions of its rows.
-template <int RB>
+// ---------------------------------------------------------------------------
+// The unit a workgroup serves: its group's keys and the question of the lane's row.
 struct CtxUnit {
   int g, qa;
   int ctx_len, slot_k;                             // key-range length; slot index of this chunk's states
   int64_t pos_base;                                // position of the first context token (fused step)
   int pa, pe;                                      // INSTR: the prompts behind the instruction
   int row0, nrows;                                 // first row of the unit; rows of the group's active questions
-  int qsel[RB];                                    // question of the lane's row in each row block (-1: none)
+  int qsel;                                        // question of the lane's row (-1: none)
   int64_t k0, k1;                                  // the chunk's tokens in the pool, k1 > k0
 };
 
 // Locates the workgroup's unit of RW rows; false if it has nothing to stream.
-// The lane's rows are row0 + first + 16 * rb, and lanes below `lead` hold each
-// of the wave's rows once.
-template <bool FUSED, int RW, int RB, bool INSTR, int TILE>
-__device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<RB>& cu, int first, int lead, int lane) {
+// The lane's row is row0 + first, and lanes below `lead` hold each of the
+// wave's rows once.
+template <bool FUSED, int RW, bool INSTR, int TILE>
+__device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit& cu, int first, int lead, int lane) {
   // instruction units follow the context units (blockIdx >= ctx_blocks)
   const unsigned ub = INSTR ? blockIdx.x - static_cast<unsigned>(p.ctx_blocks) : blockIdx.x;
   const int nrg = INSTR ? p.nrg_i : p.nrg;
@@ -503,23 +488,15 @@ __device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<R
   if (row0 >= (qb - qa) * G) return false;              // beyond every question's rows
   // the unit's rows are those of the active questions, compacted: row r is
   // head g*G + r % G of the (r / G)-th active question of [qa, qb)
-  int kq[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) kq[rb] = (row0 + first + 16 * rb) / G;
-  const int nrows = active_questions<RB>(p.active, qa, qb, kq, cu.qsel, lane) * G;
+  const int row = row0 + first;
+  const int nrows = active_questions(p.active, qa, qb, row / G, cu.qsel, lane) * G;
   if (row0 >= nrows) return false;                       // no active rows here: no tile is read
   if (static_cast<int64_t>(chunk) * cb >= ctx_len) {
     // past the prompt's context: an empty state (max -inf) for each row, so
     // that the merge can fold every chunk slot without knowing the prompt
-    if (lane < lead) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int row = row0 + first + 16 * rb;
-        if (row < nrows) {
-          const int64_t slot = (static_cast<int64_t>(slot_k) * p.Nt + cu.qsel[rb]) * p.Hq + g * G + row % G;
-          *reinterpret_cast<float2*>(p.part_ml + 2 * slot) = make_float2(-INFINITY, 0.f);
-        }
-      }
+    if (lane < lead && row < nrows) {
+      const int64_t slot = (static_cast<int64_t>(slot_k) * p.Nt + cu.qsel) * p.Hq + g * G + row % G;
+      *reinterpret_cast<float2*>(p.part_ml + 2 * slot) = make_float2(-INFINITY, 0.f);
     }
     return false;
   }
@@ -542,8 +519,8 @@ __device__ __forceinline__ bool find_context_unit(const StepParams& p, CtxUnit<R
 // context's end; a row of a fused instruction unit sits at instr_len +
 // ctx_len[b] + seg_len of its own question, b being the prompt (among
 // pa..pe-1) that holds it.
-template <int RB, bool FUSED, bool INSTR>
-__device__ __forceinline__ int64_t row_position(const StepParams& p, const CtxUnit<RB>& cu, int qi) {
+template <bool FUSED, bool INSTR>
+__device__ __forceinline__ int64_t row_position(const StepParams& p, const CtxUnit& cu, int qi) {
   if constexpr (INSTR && FUSED) {
     int lo = cu.pa, hi = cu.pe - 1;
     while (lo < hi) {
@@ -555,16 +532,17 @@ __device__ __forceinline__ int64_t row_position(const StepParams& p, const CtxUn
   return static_cast<int64_t>(cu.ctx_len) + cu.pos_base;
 }
 
-template <typename T, int D, int NW, int NS, bool FUSED, int RB, bool INSTR = false>
+// Context unit of 16 rows a wave.
+template <typename T, int D, int NW, int NS, bool FUSED, bool INSTR>
 __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char* ring, int wave, int lane) {
   using RG = Ring<T, D, NS>;
   using M = Mfma<T>;
-  using RL = RowLoads<T, D, FUSED, RB>;
-  constexpr int RW = 16 * RB * NW, DPT = RG::BLOCKS / NW;
+  using RL = RowLoads<T, D, FUSED>;
+  constexpr int RW = 16 * NW, DPT = RG::BLOCKS / NW;
   constexpr int P0 = RG::NS - 1 < 3 ? RG::NS - 1 : 3;      // tiles issued before the queries are rotated
   const int lr = lane & 15, lg = lane >> 4;
-  CtxUnit<RB> cu;
-  if (!find_context_unit<FUSED, RW, RB, INSTR, 32>(p, cu, 16 * RB * wave + lr, 16, lane)) return;
+  CtxUnit cu;
+  if (!find_context_unit<FUSED, RW, INSTR, 32>(p, cu, 16 * wave + lr, 16, lane)) return;
   const int G = p.G, g = cu.g;
   const int64_t k0 = cu.k0, k1 = cu.k1;
   const int ntiles = static_cast<int>((k1 - k0 + 31) >> 5);
@@ -572,22 +550,15 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
   const T* vbase = static_cast<const T*>(p.ctx_vt) + static_cast<int64_t>(g) * p.pool * D;
   const uint32_t lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ring));
 
-  // this lane's rows: row block rb of wave w holds rows 16*(RB*w + rb) + lr
-  // of the unit, row r being head g*G + r % G of active question qsel (rows
-  // past the active ones read question qa's inputs and are never published)
-  int qi[RB], h[RB];
-  bool in_range[RB];
-  int64_t row_base[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int row = cu.row0 + 16 * (RB * wave + rb) + lr;
-    in_range[rb] = row < cu.nrows;
-    qi[rb] = in_range[rb] ? cu.qsel[rb] : cu.qa;
-    h[rb] = g * G + row % G;
-    row_base[rb] = row_position<RB, FUSED, INSTR>(p, cu, qi[rb]);
-  }
+  // this lane's row: wave w holds rows 16*w + lr of the unit, row r being
+  // head g*G + r % G of active question qsel (rows past the active ones read
+  // question qa's inputs and are never published)
+  const int row = cu.row0 + 16 * wave + lr;
+  const bool in_range = row < cu.nrows;
+  const int qi = in_range ? cu.qsel : cu.qa, h = g * G + row % G;
+  const int64_t row_base = row_position<FUSED, INSTR>(p, cu, qi);
   RL rl;
-  issue_row_loads<T, D, FUSED, RB>(rl, p, qi, h, lg);
+  issue_row_loads<T, D, FUSED>(rl, p, qi, h, lg);
   TileOffsets<T, D, NW, NS> toff;
   toff.init(wave, lane);
   // exactly P0 tiles go out before the one wait for the row loads (a unit
@@ -600,29 +571,21 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
     issue_tile<T, D, NW, NS>(lds + t * RG::STAGE, kbase, vbase, k0 + 32ll * min(t, ntiles - 1), k1, wave, lane, toff);
   wait_row_loads<(P0 * DPT < 63 ? P0 * DPT : 63)>(rl);
 
-  bool act[RB];
-  bool any_act = false;
   const bool quad = (G & 3) == 0;                   // lane quads hold heads of one question
-  typename M::Frag qf[RB][D / 32];
+  typename M::Frag qf[1][D / 32];                   // (one 16-row block)
+  const int s_raw = static_cast<int>(rl.s);
+  const bool act = in_range && rl.a != 0u && usable_seg_len(p, s_raw) >= 0;
+  row_query<T, D, FUSED, RL::QN, (RL::TN > 0 ? RL::TN : 1)>(qf[0], rl.q, rl.th, row_base + s_raw, quad, lane);
+  if (!act) {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int s_raw = static_cast<int>(rl.s[rb]);
-    act[rb] = in_range[rb] && rl.a[rb] != 0u && usable_seg_len(p, s_raw) >= 0;
-    any_act = any_act || act[rb];
-    row_query<T, D, FUSED, RL::QN, (RL::TN > 0 ? RL::TN : 1)>(qf[rb], rl.q[rb], rl.th, row_base[rb] + s_raw,
-                                                              quad, lane);
-    if (!act[rb]) {
-#pragma unroll
-      for (int ds = 0; ds < D / 32; ++ds) qf[rb][ds] = M::zero();
-    }
+    for (int ds = 0; ds < D / 32; ++ds) qf[0][ds] = M::zero();
   }
-  const bool live = wave_any(any_act);                // wave-uniform
+  const bool live = wave_any(act);                  // wave-uniform
 #pragma unroll
   for (int t = P0; t < RG::NS - 1; ++t)
     if (t < ntiles) issue_tile<T, D, NW, NS>(lds + t * RG::STAGE, kbase, vbase, k0 + 32ll * t, k1, wave, lane, toff);
-  RowState<D> st[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) row_init(st[rb]);
+  RowState<D> st[1];
+  row_init(st[0]);
   const float c = p.c;
 
   // ring: tile t sits in stage t % NS; at iteration t the stage of tile t-1
@@ -635,11 +598,11 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
     // P^T V on the MFMA) while the scores of tile t+1 are computed, so each
     // wave has independent MFMA and VALU work in flight.  K of tile t+1 and
     // V of tile t are both in the ring during iteration t.
-    f32x4_t sa[RB][2], sb[RB][2];
+    f32x4_t sa[1][2], sb[1][2];
     // tile 0's blocks are this thread's oldest DMAs; tiles 1 .. min(NS-2, last) are younger
     wait_tiles<DPT, RG::NS - 2>(min(last, RG::NS - 2));
     __syncthreads();
-    if (live) qk_tile<T, D, NS, RB>(ring, qf, sa, lr, lg);
+    if (live) qk_tile<T, D, NS, 1>(ring, qf, sa, lr, lg);
     // iteration t < last folds the scores of full tile t and computes those
     // of tile t+1; unrolled by two so that the two score sets (sa, sb) swap
     // roles instead of being copied.  The last tile (possibly partial) is
@@ -656,7 +619,7 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
         issue_tile<T, D, NW, NS>(lds + ((t + RG::NS - 1) % RG::NS) * RG::STAGE, kbase, vbase,
                                  k0 + 32ll * (t + RG::NS - 1), k1, wave, lane, toff);
       if (live)
-        pipe_step<T, D, NS, RB>(ring + ((t + 1) % RG::NS) * RG::STAGE, ring + (t % RG::NS) * RG::STAGE, qf, sa, sb,
+        pipe_step<T, D, NS, 1>(ring + ((t + 1) % RG::NS) * RG::STAGE, ring + (t % RG::NS) * RG::STAGE, qf, sa, sb,
                                 st, 32, lr, lg, c);
       wait_tiles<DPT, RG::NS - 3>(min(last - t - 2, RG::NS - 3));
       __syncthreads();
@@ -664,7 +627,7 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
         issue_tile<T, D, NW, NS>(lds + ((t + RG::NS) % RG::NS) * RG::STAGE, kbase, vbase, k0 + 32ll * (t + RG::NS),
                                  k1, wave, lane, toff);
       if (live)
-        pipe_step<T, D, NS, RB>(ring + ((t + 2) % RG::NS) * RG::STAGE, ring + ((t + 1) % RG::NS) * RG::STAGE, qf, sb,
+        pipe_step<T, D, NS, 1>(ring + ((t + 2) % RG::NS) * RG::STAGE, ring + ((t + 1) % RG::NS) * RG::STAGE, qf, sb,
                                 sa, st, 32, lr, lg, c);
     }
     if (t < last) {
@@ -674,12 +637,12 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
         issue_tile<T, D, NW, NS>(lds + ((t + RG::NS - 1) % RG::NS) * RG::STAGE, kbase, vbase,
                                  k0 + 32ll * (t + RG::NS - 1), k1, wave, lane, toff);
       if (live) {
-        pipe_step<T, D, NS, RB>(ring + ((t + 1) % RG::NS) * RG::STAGE, ring + (t % RG::NS) * RG::STAGE, qf, sa, sb,
+        pipe_step<T, D, NS, 1>(ring + ((t + 1) % RG::NS) * RG::STAGE, ring + (t % RG::NS) * RG::STAGE, qf, sa, sb,
                                 st, 32, lr, lg, c);
-        softmax_pv<T, D, NS, RB>(ring + (last % RG::NS) * RG::STAGE, sb, st, tail_n, lr, lg, c);
+        softmax_pv<T, D, NS, 1>(ring + (last % RG::NS) * RG::STAGE, sb, st, tail_n, lr, lg, c);
       }
     } else if (live) {
-      softmax_pv<T, D, NS, RB>(ring + (last % RG::NS) * RG::STAGE, sa, st, tail_n, lr, lg, c);
+      softmax_pv<T, D, NS, 1>(ring + (last % RG::NS) * RG::STAGE, sa, st, tail_n, lr, lg, c);
     }
   } else {
     for (int t = 0; t < ntiles; ++t) {
@@ -690,15 +653,12 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
       const int tn = t + RG::NS - 1;
       if (tn <= last)
         issue_tile<T, D, NW, NS>(lds + (tn % RG::NS) * RG::STAGE, kbase, vbase, k0 + 32ll * tn, k1, wave, lane, toff);
-      if (live) ring_tile<T, D, NS, RB>(ring + (t % RG::NS) * RG::STAGE, qf, st, t == last ? tail_n : 32, lr, lg, c);
+      if (live) ring_tile<T, D, NS, 1>(ring + (t % RG::NS) * RG::STAGE, qf, st, t == last ? tail_n : 32, lr, lg, c);
     }
   }
   wait_vmcnt<0>();                                  // no LDS-DMA may outlive the workgroup
 
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    if (act[rb]) publish_rows<D>(p, st[rb], (static_cast<int64_t>(cu.slot_k) * p.Nt + qi[rb]) * p.Hq + h[rb], lg);
-  }
+  if (act) publish_rows<D>(p, st[0], (static_cast<int64_t>(cu.slot_k) * p.Nt + qi) * p.Hq + h, lg);
 }
 
 // ---------------------------------------------------------------------------
@@ -715,8 +675,9 @@ __device__ __forceinline__ void context_unit(const StepParams& p, unsigned char*
 // K(t + 1) and V(t), has landed when the phase ends.
 //
 // Queries stay as append_kernel rounds them (RAW softmax), so the fused and
-// the separate call give the same sums.  A tile past the last is not fetched,
-// and every wait counts the real fetches only.
+// the separate call give the same sums.  Past the last tile nothing is fetched
+// but the odd one that completes a pair (KS = 2: a repeat, its keys masked and
+// its values zeroed), and every wait counts the fetches with lanes only.
 //
 // What bounds it: up to about 64 rows a compute unit the latency of a tile's
 // chain (fragments, scores, softmax, products), which the 16x16x32 loop of
@@ -739,13 +700,13 @@ __device__ __forceinline__ void context_unit_pp(const StepParams& p, unsigned ch
   PpQuery<D> query;
   if (FUSED && quad) query.load_theta(p.inv_freq, lane);   // shares the lookups' round trips
   const int grp = wave >> 2, rw = KS == 1 ? wave : wave & 3;
-  CtxUnit<1> cu;
-  if (!find_context_unit<FUSED, 256 / KS, 1, INSTR, 64>(p, cu, 32 * rw + (lane & 31), 32, lane)) return;
+  CtxUnit cu;
+  if (!find_context_unit<FUSED, 256 / KS, INSTR, 64>(p, cu, 32 * rw + (lane & 31), 32, lane)) return;
   const int row = cu.row0 + 32 * rw + (lane & 31);
   const bool in_range = row < cu.nrows;
-  const int qi = in_range ? cu.qsel[0] : cu.qa;    // (rows past the active ones are never published)
+  const int qi = in_range ? cu.qsel : cu.qa;       // (rows past the active ones are never published)
   const int h = cu.g * p.G + row % p.G;
-  const int64_t base = row_position<1, FUSED, INSTR>(p, cu, qi);
+  const int64_t base = row_position<FUSED, INSTR>(p, cu, qi);
   if constexpr (FUSED) {
     if (quad) {
 #pragma unroll
@@ -1259,27 +1220,23 @@ __device__ __forceinline__ void segment_unit(const StepParams& p, UnitLds<T, D, 
 // Workgroups are dispatched in order, so segment units start as context
 // units retire and fill the tail of the context work.
 // ---------------------------------------------------------------------------
-// The second launch bound asks for four waves per SIMD, and for two in the
+// KS: the two-group unit (1: 256 rows, 2: 128), or 0 for 16 rows a wave.  The
+// second launch bound asks for four waves per SIMD, and for two in the
 // two-group unit (32 rows' accumulators and fragments ahead); the ring's LDS
 // then sets the workgroups per compute unit: one with nine stages, two with
 // five.
-template <typename T, int D, int NW>
-constexpr bool kTwoGroups = NW == 8 && D == 128 && sizeof(T) == 2;   // 256 rows with RB = 2, 128 with RB = 1
-
-template <typename T, int D, int NW, int NS, bool FUSED, int RB>
-__global__ __launch_bounds__(64 * NW, (kTwoGroups<T, D, NW> ? 2 : 4)) void attend_kernel(StepParams p) {
+template <typename T, int D, int NW, int NS, bool FUSED, int KS>
+__global__ __launch_bounds__(64 * NW, (KS > 0 ? 2 : 4)) void attend_kernel(StepParams p) {
   __shared__ UnitLds<T, D, NW, NS> sh;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = static_cast<int>(blockIdx.x);
-  constexpr bool kPp = kTwoGroups<T, D, NW>;
-  constexpr int KS = RB == 2 ? 1 : 2;
   if (blk < p.ctx_blocks) {
-    if constexpr (kPp) context_unit_pp<KS, FUSED, false>(p, sh.main, wave, lane);
-    else context_unit<T, D, NW, NS, FUSED, RB>(p, sh.main, wave, lane);
+    if constexpr (KS > 0) context_unit_pp<KS, FUSED, false>(p, sh.main, wave, lane);
+    else context_unit<T, D, NW, NS, FUSED, false>(p, sh.main, wave, lane);
   } else if (blk < p.ctx_blocks + p.instr_blocks) {
-    if constexpr (kPp) context_unit_pp<KS, FUSED, true>(p, sh.main, wave, lane);
-    else context_unit<T, D, NW, NS, FUSED, RB, true>(p, sh.main, wave, lane);
+    if constexpr (KS > 0) context_unit_pp<KS, FUSED, true>(p, sh.main, wave, lane);
+    else context_unit<T, D, NW, NS, FUSED, true>(p, sh.main, wave, lane);
   } else segment_unit<T, D, NW, NS, FUSED>(p, sh, blk - p.ctx_blocks - p.instr_blocks, wave, lane);
 }
 
@@ -1390,10 +1347,10 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(StepParams p) {
 }
 
 // ---------------------------------------------------------------------------
-template <typename T, int D, int NW, int NS, int RB>
+template <typename T, int D, int NW, int NS, int KS>
 static hipError_t launch_attend(int grid, const StepParams& p, hipStream_t s) {
-  if (p.fused) attend_kernel<T, D, NW, NS, true, RB><<<grid, 64 * NW, 0, s>>>(p);
-  else attend_kernel<T, D, NW, NS, false, RB><<<grid, 64 * NW, 0, s>>>(p);
+  if (p.fused) attend_kernel<T, D, NW, NS, true, KS><<<grid, 64 * NW, 0, s>>>(p);
+  else attend_kernel<T, D, NW, NS, false, KS><<<grid, 64 * NW, 0, s>>>(p);
   return hipGetLastError();
 }
 
@@ -1401,8 +1358,8 @@ static hipError_t launch_attend(int grid, const StepParams& p, hipStream_t s) {
 template <typename T, int D, int NW>
 static hipError_t launch_ring(bool deep, int grid, const StepParams& p, hipStream_t s) {
   if constexpr (sizeof(T) == 4)
-    if (deep) return launch_attend<T, D, NW, ring_stages(sizeof(T), D, true), 1>(grid, p, s);
-  return launch_attend<T, D, NW, ring_stages(sizeof(T), D, false), 1>(grid, p, s);
+    if (deep) return launch_attend<T, D, NW, ring_stages(sizeof(T), D, true), 0>(grid, p, s);
+  return launch_attend<T, D, NW, ring_stages(sizeof(T), D, false), 0>(grid, p, s);
 }
 
 template <typename T, int D>
@@ -1410,7 +1367,7 @@ static hipError_t launch_waves(int waves, int rb, bool deep, int grid, const Ste
   // bf16 at D = 128 with eight waves is the two-group unit
   if constexpr (sizeof(T) == 2 && D == 128) {
     constexpr int kStages = ring_stages(sizeof(T), D, true);
-    if (waves == 8) return rb == 2 ? launch_attend<T, D, 8, kStages, 2>(grid, p, s) : launch_attend<T, D, 8, kStages, 1>(grid, p, s);
+    if (waves == 8) return rb == 2 ? launch_attend<T, D, 8, kStages, 1>(grid, p, s) : launch_attend<T, D, 8, kStages, 2>(grid, p, s);
   }
   if (rb != 1) return hipErrorInvalidValue;
   switch (waves) {
