@@ -134,9 +134,9 @@ ippd_status_t prefill(const ippd_batch_t* bt, bool shared, int32_t max_q_tokens,
   p.B = bt->num_prompts; p.Nt = bt->num_questions; p.Hq = bt->num_q_heads; p.Hkv = bt->num_kv_heads;
   p.G = bt->num_q_heads / bt->num_kv_heads; p.D = bt->head_dim; p.seg_cap = bt->seg_capacity;
   p.max_ctx_len = bt->max_ctx_len;
-  p.shared = pl.shared; p.tb = pl.tb; p.n_groups = pl.n_groups; p.gps = pl.gps;
+  p.shared = pl.shared; p.tb = pl.tb; p.n_groups = pl.n_groups;
   p.kq = pl.kq; p.kc = pl.kc; p.q_blocks = pl.q_blocks;
-  p.n_cgroups = pl.n_cgroups; p.gps_c = pl.gps_c;
+  p.n_cgroups = pl.n_cgroups;
   p.S = bt->num_instr;
   p.max_instr_len = bt->num_instr > 0 ? bt->max_instr_len : 0;
   p.instr_start = bt->num_instr > 0 ? bt->instr_start : nullptr;

@@ -104,10 +104,10 @@ struct StepPlan {
 // which holds every unit of groups g = 8 j + (u & 7).
 struct PrefillPlan {
   int shared, waves, rb, tb;
-  int n_groups, gps;       // question-row groups, and groups per XCD slice (ceil(n_groups / 8))
-  int n_cgroups, gps_c;    // context-row groups: n_groups, then the instruction groups
+  int n_groups;            // question-row groups
+  int n_cgroups;           // context-row groups: n_groups, then the instruction groups
   int kq, kc;              // question-row and context-row units per group
-  int q_blocks, grid;      // 8 * gps * kq, then + 8 * gps_c * kc
+  int q_blocks, grid;      // kq units of the groups rounded up to 8, then + kc of the context-row groups, so rounded
 };
 
 struct PrefillParams {
@@ -120,8 +120,7 @@ struct PrefillParams {
   float* out_seg;          // [Nt][seg_cap][Hq][D]
   int64_t pool;
   int B, Nt, Hq, Hkv, G, D, seg_cap, max_ctx_len;
-  int shared, tb, n_groups, gps, kq, kc, q_blocks;
-  int n_cgroups, gps_c;
+  int shared, tb, n_groups, n_cgroups, kq, kc, q_blocks;
   // two-level batch (S > 0): instruction s at pool rows instr_off[s] .. + instr_len[s]
   const int32_t* instr_start; const int64_t* instr_off; const int32_t* instr_len;
   int S, max_instr_len;

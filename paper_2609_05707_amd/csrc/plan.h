@@ -473,9 +473,7 @@ inline bool plan_prefill(const ippd_batch_t* bt, bool shared, int32_t max_q_toke
   pl->rb = rb;
   pl->tb = tb;
   pl->n_groups = static_cast<int>(n_groups);
-  pl->gps = static_cast<int>(gps);
   pl->n_cgroups = static_cast<int>(n_cgroups);
-  pl->gps_c = static_cast<int>(gps_c);
   pl->kq = static_cast<int>(kq);
   pl->kc = static_cast<int>(kc);
   pl->q_blocks = static_cast<int>(q_blocks);
