@@ -24,7 +24,8 @@ from collections import defaultdict
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-KERNEL_SOURCES = ("decode_step.hip", "tile_attend.h", "ippd_device.h", "ippd_internal.h", "ippd_api.hip")
+KERNEL_SOURCES = ("decode_step.hip", "prefill_pingpong.h", "tile_attend.h", "ippd_device.h", "ippd_internal.h",
+                  "ippd_api.hip", "plan.h")
 
 
 def code_only(text: str) -> str:

@@ -69,6 +69,24 @@ def test_prefill_flops_by_hand():
     assert BP.flops(st, True, ins) == per * (2 * ins_rows + 2 * ctx_i + q_i)
 
 
+def test_counter_fingerprint_covers_every_source_of_a_decode_call():
+    """The planner and the kernels of a decode call, and whatever they include
+    (the public header, declarations only, aside): a change of any of them
+    makes an older counter record stale."""
+    import re
+    from paper_2609_05707_amd import traffic as T
+    src = os.path.join(ROOT, "paper_2609_05707_amd", "csrc")
+    need, todo = set(), ["ippd_api.hip", "decode_step.hip"]
+    while todo:
+        f = todo.pop()
+        if f in need:
+            continue
+        need.add(f)
+        with open(os.path.join(src, f)) as fh:
+            todo += [x for x in re.findall(r'^#include "([^"]+)"', fh.read(), re.M) if x != "ippd.h"]
+    assert need == set(T.KERNEL_SOURCES)
+
+
 def test_counter_fingerprint_ignores_comments_but_not_code(tmp_path):
     """A counter record stays valid across comment and layout edits of the
     kernel sources, and not across a code change."""
