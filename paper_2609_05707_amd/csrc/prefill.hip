@@ -751,9 +751,10 @@ __global__ __launch_bounds__(512, 2) void prefill_pingpong_kernel(PrefillParams 
   pingpong_unit<D, KS>(p, sh, wave, lane);
 }
 
-// Waves and 16-row blocks per wave of a unit: bf16 units have eight waves of
-// two blocks, fp32 ones (operands twice as wide) one block per wave, and four
-// waves at D = 128 (32 KB stages).
+// A unit's waves, and its rows as rb 16-row blocks per wave: bf16 units have
+// eight waves and 256 rows (rb = 2; the planner halves them, rb = 1, to 128
+// rows whose keys the two groups share), fp32 ones (operands twice as wide)
+// one block per wave, and four waves at D = 128 (32 KB stages).
 bool prefill_variant(int dtype, int head_dim, int* waves, int* rb) {
   const bool bf = dtype == IPPD_DTYPE_BF16;
   if (head_dim != 64 && head_dim != 128) return false;

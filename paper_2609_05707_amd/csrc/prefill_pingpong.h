@@ -17,7 +17,7 @@
 // block of the cache) is 16 contiguous bytes.
 //
 // What bounds it: per 64 keys a wave issues 32 products (1024 matrix-core
-// cycles) and about 700 cycles of vector work (max, 32 exp2 at quarter rate,
+// cycles) and the softmax's vector work (max, 32 exp2 at quarter rate,
 // packing, row sums).  A SIMD holds two waves; if both do the same thing at
 // the same time the two kinds of work add up.  So waves 0-3 and 4-7 (one of
 // each group per SIMD) run half a step apart, separated by workgroup
@@ -48,9 +48,11 @@ struct PpRing {
   static constexpr int HB = HALF / 1024;              // 1 KB DMA blocks per half (keys; values the same)
 };
 
-// One 16-byte LDS-DMA as dma16s, issued with every lane (on = ~0) or none (0):
-// with none it moves nothing but still counts, so the number of DMAs in
-// flight does not depend on how many tiles are left.  No memory clobber: it
+// One 16-byte LDS-DMA as dma16s, issued with every lane (on = ~0) or none (0),
+// so that the steps past the last fetch run the same code.  One without lanes
+// moves nothing.  The waits allow for the younger fetches with lanes only, so
+// they hold whether or not the others are counted as in flight: counting them
+// can only make a wait longer.  No memory clobber: it
 // fills stages that no LDS read of its phase touches, and its order against
 // the barriers is that of any volatile asm.
 __device__ __forceinline__ void dma16s_if(const void* sbase, uint32_t voff, uint32_t lds_block, uint32_t on) {
