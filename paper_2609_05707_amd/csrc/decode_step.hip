@@ -1,7 +1,7 @@
 // IPPD decode-step attention on gfx950: two launches per call.
 //
 //   attend_kernel  context units (group, chunk, row group): shared-context
-//                  attention of 16*NW query rows over one chunk of context
+//                  attention of the unit's query rows over one chunk of context
 //                  tokens, one unnormalised partial softmax state (running
 //                  max, sum, weighted values) per row; then segment units,
 //                  seg_tpu tasks (question i, kv head g) each: in the fused
@@ -15,9 +15,9 @@
 // The launch boundary orders the two, so no unit ever waits for another.
 //
 // A *group* is (prompt b, kv head g) for IPPD or (question i, kv head g) for
-// the standard baseline.  A context unit streams context tokens
-// [chunk*C, (chunk+1)*C) of its group against 16*NW query rows, the
-// (question, head of group g) pairs of the prompt in order.  IPPD serves all
+// the standard baseline.  A context unit streams one of the equal chunks of
+// its group's context against 16*NW query rows (two-group units: 128 or 256),
+// the (active question, head of group g) pairs of the prompt in order.  IPPD serves all
 // questions of the prompt from one pass over the chunk, so K_c and V_c come
 // from HBM once for all M_j queries (Sec. 4.3); the baseline serves the G
 // rows of one question and reads the context once per question (App. A.2.2,
@@ -35,6 +35,9 @@
 // are XOR-swizzled in 16-byte chunks so that the 16 lanes of every ds_read
 // hit distinct bank groups of the 64-bank LDS.
 //
+// That is context_unit.  With more rows at bf16, D = 128 (context_unit_pp) two
+// wave groups take turns at the matrix cores over 64-key tiles, as in
+// prefill_pingpong.h.
 #include <float.h>
 #include <stddef.h>
 
